@@ -145,10 +145,11 @@ typedef struct {
                          around the soft alignment, a few hundred columns wide on long
                          similar series).  1: sweep every tile                            */
   int32_t walk;       /* path recovery of wts_dba_iterate / wts_dtw_align with paths:
-                         WTS_WALK_STRIPS (1): the path sweep tags every cell with the cell
-                         through which its path enters the strip, and all strips are then
-                         walked at once; WTS_WALK_PAIRS (2): the sweep keeps only the argmin
-                         codes (about a tenth faster) and each pair walks its strips in turn;
+                         WTS_WALK_STRIPS (1): the path sweep keeps every cell's argmin code
+                         and tags it with the cell through which its path enters the strip,
+                         and all strips are then walked at once; WTS_WALK_PAIRS (2): the sweep
+                         keeps checkpoints only (a fifth to a third faster), and each pair
+                         sweeps the tiles its path crosses again and walks its strips in turn;
                          WTS_WALK_AUTO (0, default): pairs when the batch's cells outweigh
                          its longest pair's walk (large batches), else strips.  Paths,
                          counts and sums are the same bits either way                      */

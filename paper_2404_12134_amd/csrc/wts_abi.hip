@@ -58,7 +58,7 @@ struct PairSet {
   int64_t code_words = 0, bnd_elems = 0, aux_strip_elems = 0, state_elems = 0, row_elems = 0;
   int64_t max_rows = 0;
   int rho = 4;   // barycenter rows per lane of this set's sweeps
-  bool walk_pairs = false;   // path recovery one pair at a time (PATH sweep, no entry tags)
+  bool walk_pairs = false;   // path recovery one pair at a time, from checkpoints (CKPT sweep)
 };
 
 struct Job {
@@ -66,7 +66,7 @@ struct Job {
   int32_t M, N, out;
 };
 
-void build_set(PairSet& ps, std::vector<Job> jobs, int rho) {
+void build_set(PairSet& ps, std::vector<Job> jobs, int rho, bool soft) {
   const int H = wts::kWave * rho;
   ps.rho = rho;
   std::stable_sort(jobs.begin(), jobs.end(), [](const Job& a, const Job& b) {
@@ -86,6 +86,7 @@ void build_set(PairSet& ps, std::vector<Job> jobs, int rho) {
     d.S = (jb.M + H - 1) / H;
     d.out = jb.out;
     d.WT = (jb.N + wts::kWave - 1 + 15) / 16;
+    if (!soft) d.WT = (d.WT + 1) & ~1;   // code words hold 32 steps
     d.code_base = code;
     d.bnd_base = bnd;
     d.aux_base = aux;
@@ -96,7 +97,8 @@ void build_set(PairSet& ps, std::vector<Job> jobs, int rho) {
     code += (int64_t)d.S * d.WT * rho * wts::kWave;
     bnd += jb.N;
     aux += (int64_t)d.S * jb.N;
-    state += (int64_t)d.S * d.WT * (rho + 1) * wts::kWave;
+    // checkpoints: every 16 steps (Soft-DTW), every 64 steps (DTW paths)
+    state += (int64_t)d.S * (soft ? d.WT : (d.WT + 3) / 4) * (rho + 1) * wts::kWave;
     flags += d.S;
     rows += (int64_t)d.S * ((jb.N + wts::kWave - 1 + 3) & ~3);   // strip row stride RS
     for (int s = 0; s < d.S; ++s) ps.items.push_back(make_int2((int)p, s));
@@ -126,7 +128,7 @@ void build_set(PairSet& ps, std::vector<Job> jobs, int rho) {
 // Workspace: every region 256-byte aligned, in this order.
 struct Layout {
   size_t queue = 0, progress = 0, bnd_r = 0, bnd_aux = 0, codes = 0, out_dist = 0, out_aux = 0;
-  size_t seg = 0, seg_len = 0, seg_off = 0, runs = 0, psum = 0, pcnt = 0, dm = 0, totals = 0;
+  size_t seg = 0, runs = 0, dm = 0, totals = 0;
   size_t rows = 0, states = 0, push_up = 0, push_dg = 0, gsum = 0, hsum = 0, out_end = 0;
   size_t total = 0;
 };
@@ -147,13 +149,21 @@ void* g_scratch[kMaxDevices] = {};
 // chain, and the dispatcher does not spread workgroups perfectly once they
 // cover nearly every compute unit: such batches take 5 rows per lane when
 // that brings them under ~80 % of the SIMDs.  Small batches (one strip per
-// SIMD or less) and large ones (several per SIMD) keep 4.
-int bary_rho(int64_t L, int n, int cus) {
-  auto items = [&](int r) { return (int64_t)n * ((L + 64 * r - 1) / (64 * r)); };
+// SIMD or less) keep 4.  Large float64 batches of two channels or more take 5
+// where the padding of the last strip allows it: a step costs about 2 d + 4
+// instructions a row and 10 of its own, which 5 rows share (512 cycles of
+// 1k-20k samples, d = 6, L = 10,000: the checkpointed sweep 19.4 ms against
+// 20.7; the score sweep at d = 6 13 % and at d = 3 6 % faster).  At d = 1 the
+// two time alike, and in float32 the score sweep is 10 % slower at 5.
+int bary_rho(int64_t L, int n, int cus, int d, bool fp32) {
+  auto strips = [&](int r) { return (L + 64 * r - 1) / (64 * r); };
+  auto items = [&](int r) { return (int64_t)n * strips(r); };
   const int64_t simds = 4 * (int64_t)cus;
   const int64_t cap = simds * 13 / 16;
   const int64_t i4 = items(4);
   if (i4 > cap && i4 <= 2 * simds && items(5) <= cap) return 5;
+  auto steps = [&](int r) { return strips(r) * (r * (2 * d + 4) + 10); };
+  if (i4 > 2 * simds && d >= 2 && !fp32 && steps(5) < steps(4)) return 5;
   return 4;
 }
 
@@ -242,19 +252,17 @@ Layout layout(const wts_plan* p, int op) {
   l.queue = take(2 * sizeof(int));   // [0] item counter, [1] status word
   l.bnd_r = take(sizeof(double) * (size_t)ps.row_elems);
   l.bnd_aux = take(sizeof(int) * (size_t)(op == WTS_OP_MEDOID ? 0 : ps.row_elems));
-  if (paths) l.codes = take(sizeof(uint32_t) * (size_t)ps.code_words);
+  if (paths && ps.walk_pairs)
+    l.states = take((p->opts.decision == WTS_DECISION_FP32 ? sizeof(float) : sizeof(double)) *
+                    (size_t)ps.state_elems);
+  else if (paths)
+    l.codes = take(sizeof(uint32_t) * (size_t)ps.code_words);
   l.out_dist = take(sizeof(double) * (size_t)ps.n_pairs);
   l.out_aux = take(sizeof(int) * (size_t)ps.n_pairs);
   if (op == WTS_OP_SUBDTW) l.out_end = take(sizeof(int) * (size_t)ps.n_pairs);
   if (paths) {
-    l.seg = take(sizeof(int2) * (size_t)ps.n_items);
-    l.seg_len = take(sizeof(int) * (size_t)ps.n_items);
-    l.seg_off = take(sizeof(int) * (size_t)ps.n_items);
-  }
-  if (op == WTS_OP_DBA) {
-    if (ps.walk_pairs) l.runs = take(sizeof(int2) * (size_t)p->n * (size_t)p->L);
-    l.psum = take(sizeof(double) * (size_t)p->n * (size_t)p->L * (size_t)p->d);
-    l.pcnt = take(sizeof(int) * (size_t)p->n * (size_t)p->L);
+    if (!ps.walk_pairs) l.seg = take(sizeof(int2) * (size_t)ps.n_items);
+    l.runs = take(sizeof(int2) * (size_t)p->n * (size_t)p->L);
   }
   if (op == WTS_OP_MEDOID) {
     l.dm = take(sizeof(double) * (size_t)p->n * (size_t)p->n);
@@ -267,12 +275,16 @@ Layout layout(const wts_plan* p, int op) {
 template <typename T>
 T* at(void* ws, size_t off) { return reinterpret_cast<T*>(static_cast<char*>(ws) + off); }
 
-// Path recovery.  Tagging every cell with its strip entry (PATHT) costs the
-// sweep about a tenth of its time (two selects of about 22 operations per
-// cell) and lets all strips be walked at once; without the tags (PATH) each
-// pair walks its strips in turn, about 85 us per strip on gfx950.  The pair
-// walk pays when the tags' tenth, about 1e-13 s per cell on 256 CUs, exceeds
-// the longest pair's walk.
+// Path recovery.  Codes and entry tags for every cell (PATHT) cost the sweep
+// a fifth to a third of its time and let all strips be walked at once, in
+// about 0.1 ms.  From checkpoints (CKPT) the sweep is the value sweep, and
+// each pair's strips are swept again along its path and walked in turn, about
+// 35 us a strip.  Measured per DBA iteration, codes against checkpoints: 512
+// cycles of 1k-20k samples (L = 10,000, 3.2e10 cells) 25.4 / 22.8 ms, 40
+// cycles of 40k-50k samples in float32 decisions 51.9 / 40.0 ms, 64 cycles of
+// 4k-6k samples 1.46 / 1.42 ms, 24 cycles of 1.5k-2.5k samples 0.79 / 0.85 ms.
+// Checkpoints pay when the codes and tags, about 1.5e-13 s a cell, cost more
+// than the longest pair's strips.
 bool walk_pairs_pays(const PairSet& ps) {
   double cells = 0.0;
   int smax = 0;
@@ -280,7 +292,7 @@ bool walk_pairs_pays(const PairSet& ps) {
     cells += (double)d.M * (double)d.N;
     smax = std::max(smax, d.S);
   }
-  return cells * 1e-13 > smax * 85e-6;
+  return cells * 1.5e-13 > smax * 35e-6;
 }
 
 int default_grid(const wts_plan* p, const PairSet& ps) {
@@ -373,14 +385,15 @@ wts_status run_sweep(const wts_plan* p, const PairSet& ps, int mode, bool euc, b
   a.y = y;
   a.bnd_r = at<double>(ws, l.bnd_r);
   a.bnd_aux = at<int>(ws, l.bnd_aux);
-  a.codes = mode == wts::MODE_PATH || mode == wts::MODE_PATHT ? at<uint32_t>(ws, l.codes) : nullptr;
+  a.codes = mode == wts::MODE_PATHT ? at<uint32_t>(ws, l.codes) : nullptr;
+  a.states = mode == wts::MODE_CKPT ? at<double>(ws, l.states) : nullptr;
   a.out_dist = out_dist ? out_dist : at<double>(ws, l.out_dist);
   a.out_aux = at<int>(ws, l.out_aux);
   a.out_end = mode == wts::MODE_SUB ? at<int>(ws, l.out_end) : nullptr;
   a.cost_kind = euc ? 1 : 0;
   a.relaxed_wait = ps.n_items > 16 * p->cus ? 1 : 0;   // > 4 items per SIMD
   const int tk = timing_begin(p, x_is_cycle ? WTS_OP_MEDOID
-                                 : mode == wts::MODE_PATH || mode == wts::MODE_PATHT ? WTS_OP_DBA
+                                 : mode == wts::MODE_CKPT || mode == wts::MODE_PATHT ? WTS_OP_DBA
                                  : mode == wts::MODE_SUB ? WTS_OP_SUBDTW : WTS_OP_SCORE, st);
   HIP_TRY(wts::launch_fwd(p->d, ps.rho, mode, euc, x_is_cycle, p->dtype,
                           p->opts.decision == WTS_DECISION_FP32, a, default_grid(p, ps), st));
@@ -388,41 +401,44 @@ wts_status run_sweep(const wts_plan* p, const PairSet& ps, int mode, bool euc, b
   return WTS_OK;
 }
 
-// The path sweep, then path recovery: segments, segment lengths and, with
-// psum, the DBA partial sums.  Pair walks: a PATH sweep, one walk per pair
-// (row runs), the row sums in parallel.  Strip walks: a PATHT sweep, the
-// strip chain from the entry tags, one walk per strip (row runs and sums).
+// The path sweep, then path recovery: the columns each barycenter row's run
+// takes of every path.  By pairs: a CKPT sweep, then one workgroup per pair
+// sweeps the tiles its path crosses again and walks them.  By strips: a PATHT
+// sweep, the strip chain from the entry tags, one walk per strip.
 wts_status run_paths(const wts_plan* p, const double* bary, const void* cycles, void* ws,
-                     const Layout& l, double* out_dist, double* psum, int* pcnt, hipStream_t st) {
+                     const Layout& l, double* out_dist, hipStream_t st) {
   const PairSet& ps = p->bary;
-  const int mode = ps.walk_pairs ? wts::MODE_PATH : wts::MODE_PATHT;
+  const int mode = ps.walk_pairs ? wts::MODE_CKPT : wts::MODE_PATHT;
   wts_status rc = run_sweep(p, ps, mode, false, false, bary, cycles, ws, l, out_dist, st);
   if (rc != WTS_OK) return rc;
-  wts::WalkArgs w{};
-  w.pairs = ps.d_pairs;
-  w.items = ps.d_items;
-  w.codes = at<uint32_t>(ws, l.codes);
-  w.y = cycles;
-  w.L = p->L;
-  w.seg_len = at<int>(ws, l.seg_len);
-  w.status = p->d_status;
-  w.skip = skip_of(p);
   if (ps.walk_pairs) {
-    w.seg_out = at<int2>(ws, l.seg);
-    w.runs = psum ? at<int2>(ws, l.runs) : nullptr;
-    HIP_TRY(wts::launch_path_walk(ps.rho, w, ps.n_pairs, st));
-    if (psum)
-      HIP_TRY(wts::launch_run_sum(p->d, p->dtype, w.runs, p->d_off, cycles, p->n, p->L, psum,
-                                  pcnt, skip_of(p), st));
+    wts::TraceArgs t{};
+    t.pairs = ps.d_pairs;
+    t.x = bary;
+    t.y = cycles;
+    t.states = at<double>(ws, l.states);
+    t.bnd_r = at<double>(ws, l.bnd_r);
+    t.runs = at<int2>(ws, l.runs);
+    t.L = p->L;
+    t.status = p->d_status;
+    t.skip = skip_of(p);
+    HIP_TRY(wts::launch_trace(p->d, ps.rho, p->dtype, p->opts.decision == WTS_DECISION_FP32, t,
+                              ps.n_pairs, st));
     return WTS_OK;
   }
   HIP_TRY(wts::launch_chain(ps.d_pairs, ps.n_pairs, at<int>(ws, l.bnd_aux),
                             at<int>(ws, l.out_aux), at<int2>(ws, l.seg), p->d_status,
                             skip_of(p), st));
+  wts::WalkArgs w{};
+  w.pairs = ps.d_pairs;
+  w.items = ps.d_items;
   w.seg = at<int2>(ws, l.seg);
-  w.psum = psum;
-  w.pcnt = pcnt;
-  HIP_TRY(wts::launch_walk(p->d, ps.rho, p->dtype, false, w, ps.n_items, st));
+  w.runs = at<int2>(ws, l.runs);
+  w.codes = at<uint32_t>(ws, l.codes);
+  w.L = p->L;
+  w.status = p->d_status;
+  w.skip = skip_of(p);
+  HIP_TRY(wts::launch_walk(ps.rho, w, ps.n_items, st));
   return WTS_OK;
 }
 
@@ -500,14 +516,15 @@ wts_status wts_plan_create(wts_plan** out, int device, int32_t n, int32_t d, int
   if (L > 0) {
     for (int k = 0; k < n; ++k)
       jobs.push_back(Job{0, p->off[k], (int32_t)L, (int32_t)(p->off[k + 1] - p->off[k]), k});
-    build_set(p->bary, jobs, o.rho ? o.rho : bary_rho(L, n, p->cus));
+    build_set(p->bary, jobs, o.rho ? o.rho : bary_rho(L, n, p->cus, d, o.decision == WTS_DECISION_FP32),
+              false);
     p->bary.walk_pairs = o.walk == WTS_WALK_PAIRS ||
                          (o.walk == WTS_WALK_AUTO && walk_pairs_pays(p->bary));
-    build_set(p->soft, jobs, wts::kSoftRho);
+    build_set(p->soft, jobs, wts::kSoftRho, true);
     std::vector<Job> tjobs;
     for (int k = 0; k < n; ++k)
       tjobs.push_back(Job{p->off[k], 0, (int32_t)(p->off[k + 1] - p->off[k]), (int32_t)L, k});
-    build_set(p->softT, tjobs, wts::kSoftRho);
+    build_set(p->softT, tjobs, wts::kSoftRho, true);
     std::vector<int64_t> base(n);
     for (int k = 0; k < n; ++k) base[k] = (int64_t)k * (L - 1) + p->off[k];
     hipError_t e;
@@ -525,7 +542,7 @@ wts_status wts_plan_create(wts_plan** out, int device, int32_t n, int32_t d, int
         if (la <= lb) jobs.push_back(Job{p->off[a], p->off[b], (int32_t)la, (int32_t)lb, slot});
         else jobs.push_back(Job{p->off[b], p->off[a], (int32_t)lb, (int32_t)la, slot});
       }
-    build_set(p->med, jobs, p->rho);
+    build_set(p->med, jobs, p->rho, false);
     if (!ab.empty()) {
       hipError_t e;
       if ((e = hipMalloc(&p->d_med_ab, sizeof(int2) * ab.size())) != hipSuccess) return cleanup_fail(e, "hipMalloc");
@@ -704,25 +721,10 @@ wts_status wts_dtw_align(const wts_plan* p, const double* bary, const void* cycl
     HIP_TRY(wts::launch_score(dist, at<int>(ws, l.out_aux), p->n, nullptr, path_len, st));
     return WTS_OK;
   }
-  rc = run_paths(p, bary, cycles, ws, l, dist, nullptr, nullptr, st);
+  rc = run_paths(p, bary, cycles, ws, l, dist, st);
   if (rc != WTS_OK) return rc;
-  const PairSet& ps = p->bary;
-  HIP_TRY(wts::launch_seg_prefix(ps.d_pairs, ps.n_pairs, at<int>(ws, l.seg_len),
-                                 at<int>(ws, l.seg_off), path_len, st));
-  wts::WalkArgs w{};
-  w.pairs = ps.d_pairs;
-  w.items = ps.d_items;
-  w.seg = at<int2>(ws, l.seg);
-  w.codes = at<uint32_t>(ws, l.codes);
-  w.y = cycles;
-  w.L = p->L;
-  w.seg_len = at<int>(ws, l.seg_len);
-  w.seg_off = at<int>(ws, l.seg_off);
-  w.path_base = p->d_path_base;
-  w.paths = paths;
-  w.status = p->d_status;
-  w.skip = skip_of(p);
-  HIP_TRY(wts::launch_walk(p->d, ps.rho, p->dtype, true, w, ps.n_items, st));
+  HIP_TRY(wts::launch_emit(at<int2>(ws, l.runs), p->d_path_base, p->n, p->L, paths, path_len,
+                           skip_of(p), st));
   return WTS_OK;
 }
 
@@ -740,10 +742,10 @@ wts_status wts_dba_iterate(const wts_plan* p, const double* bary_in, const void*
                             seg_f64(weights, p->n))) != WTS_OK)
     return rc;
   const Layout l = layout(p, WTS_OP_DBA);
-  rc = run_paths(p, bary_in, cycles, ws, l, dist, at<double>(ws, l.psum), at<int>(ws, l.pcnt), st);
+  rc = run_paths(p, bary_in, cycles, ws, l, dist, st);
   if (rc != WTS_OK) return rc;
-  HIP_TRY(wts::launch_dba_reduce(at<double>(ws, l.psum), at<int>(ws, l.pcnt), weights, p->n,
-                                 p->L, p->d, bary_out, counts, st));
+  HIP_TRY(wts::launch_run_fold(p->d, p->dtype, at<int2>(ws, l.runs), p->d_off, cycles, weights,
+                               p->n, p->L, bary_out, counts, skip_of(p), st));
   return WTS_OK;
 }
 

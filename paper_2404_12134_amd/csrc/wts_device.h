@@ -38,11 +38,11 @@ struct PairDesc {
   int32_t S;          // strips
   int32_t out;        // output slot (cycle index, or pair index for the medoid)
   int32_t flag_base;  // progress counter of strip 0
-  int32_t WT;         // code words per (strip, row, lane): ceil((N + 63) / 16) rounded
+  int32_t WT;         // 16-step groups of a strip's sweep: ceil((N + 63) / 16), even for the DTW sweeps
   int32_t item_base;  // index of this pair's strip 0 in the item list
   int32_t pad;
   int64_t aux_base;   // first element of this pair's per-strip rows (S * N)
-  int64_t state_base; // first double of this pair's Soft-DTW sweep states
+  int64_t state_base; // first value of this pair's sweep states (checkpoints)
   int64_t row_base;   // DTW sweeps: first element of this pair's strip rows (S * RS)
 };
 
@@ -79,13 +79,14 @@ __device__ __forceinline__ PairDesc uniform(const PairDesc& p) {
 // for 16 steps in registers).
 constexpr int kSoftRho = 2;
 
-// DIST: value only; DIST_LEN: value and path length; PATH: value and argmin
-// codes; SUB: Sub-DTW (free start; lowest-column minimum of the last row and
-// the start column of its path).
-// MODE_PATH keeps the argmin codes only (the path is then walked pair by
-// pair); MODE_PATHT also tags every cell with the top-row cell through which
-// its path enters the strip, so that all strips can be walked at once.
-enum Mode { MODE_DIST = 0, MODE_DIST_LEN = 1, MODE_PATH = 2, MODE_SUB = 3, MODE_PATHT = 4 };
+// DIST: value only; DIST_LEN: value and path length; SUB: Sub-DTW (free
+// start; lowest-column minimum of the last row and the start column of its
+// path).  Paths are recovered in one of two ways: MODE_CKPT is the value sweep
+// with a checkpoint of every lane's state each 64 steps, from which the tiles
+// that a path crosses are swept again; MODE_PATHT keeps the argmin codes of
+// every cell and tags it with the top-row cell through which its path enters
+// the strip, so that all strips can be walked at once.
+enum Mode { MODE_DIST = 0, MODE_DIST_LEN = 1, MODE_CKPT = 2, MODE_SUB = 3, MODE_PATHT = 4 };
 
 struct FwdArgs {
   const PairDesc* pairs;
@@ -96,10 +97,11 @@ struct FwdArgs {
   const void* x;         // X rows (float64 barycenter, or cycles for the medoid)
   const void* y;         // cycle values
   double* bnd_r;         // strip rows (S * RS per pair, sentinel-filled): cumulative cost
-  int* bnd_aux;          // strip rows: path length (DIST_LEN) or entry code (PATH)
-  uint32_t* codes;       // 2-bit argmin codes (PATH)
+  int* bnd_aux;          // strip rows: path length (DIST_LEN) or entry code (PATHT)
+  uint32_t* codes;       // argmin code planes (PATHT)
+  double* states;        // checkpoints (CKPT): per strip and 64 steps, RHO + 1 values per lane
   double* out_dist;      // [pair slot] r(M-1, N-1)
-  int* out_aux;          // [pair slot] |pi| (DIST_LEN), entry code of (M-1, N-1) (PATH) or a* (SUB)
+  int* out_aux;          // [pair slot] |pi| (DIST_LEN), entry code of (M-1, N-1) (PATHT) or a* (SUB)
   int* out_end;          // [pair slot] b* (SUB)
   int cost_kind;         // 0 squared, 1 Euclidean (sqrt)
   int relaxed_wait;      // 1: far more items than resident wavefronts; wait with long sleeps

@@ -2,6 +2,7 @@
 // initialisation for gfx950, and the float64 instances of the DTW sweep
 // (wts_sweep.h).
 #include "wts_sweep.h"
+#include "wts_walk.h"
 
 namespace wts {
 
@@ -41,252 +42,94 @@ __global__ void chain_kernel(const PairDesc* __restrict__ pairs, int n_pairs,
   }
 }
 
-constexpr int kWalkWords = 16;   // code words (per row and lane) staged in LDS at a time
-
-// Walks the optimal path through one strip, from its bottom-row crossing to
-// its top-row cell, with the strip's argmin codes staged in LDS.  All 64
-// lanes walk in lockstep (identical state), so the staging loads are
-// cooperative and the LDS reads are broadcasts.
-//   EMIT = false: per-row runs -> DBA partial sums (psum != nullptr) and the
-//                 strip's segment length;
-//   EMIT = true:  writes the segment's (i, j) pairs into the path list.
-template <typename TY, int D, int RHO, bool EMIT>
+// Walks the optimal path through one strip (one wave), from its bottom-row
+// crossing to its top-row cell (walk_strip), and records the run of columns
+// [lo, hi] that the path occupies on each row.  A walk that does not end
+// where the chain says marks the status word; its strip then contributes
+// empty runs.
+template <int RHO>
 __global__ __launch_bounds__(kWave) void walk_kernel(WalkArgs a) {
   constexpr int H = kWave * RHO;
-  __shared__ uint32_t blk[kWalkWords][RHO][kWave];
-  __shared__ int run_lo[H];
-  __shared__ int run_hi[H];
   const int lane = threadIdx.x;
   const int item = blockIdx.x;
   if (skipped(a.skip)) return;
   const int2 it = a.items[item];
-  const PairDesc pd = a.pairs[it.x];
-  const int s = it.y;
+  const PairDesc pd = uniform(a.pairs[uni(it.x)]);
+  const int s = uni(it.y);
   const int i0 = s * H;
   const int iend = min(pd.M, i0 + H) - 1;
-  const int2 sg = a.seg[item];
+  const int jx = uni(a.seg[item].x), jtop = uni(a.seg[item].y);
   const uint32_t* codes = a.codes + pd.code_base + (int64_t)s * pd.WT * RHO * kWave;
-
-  int i = iend, j = sg.x, hi = sg.x;
-  const int jstop = sg.y;
-  // An inconsistent path (the chain reported one, or the walk leaves the
-  // strip) is flagged in the status word; the strip then contributes empty
-  // row runs, so no later access depends on the bad path.
-  bool bad = sg.x < 0 || sg.x >= pd.N || sg.y < 0 || sg.y > sg.x;
-  if (bad && lane == 0) atomicOr(a.status, kStatusBadPath);
-  int wlo = 1 << 30, whi = -1;
-  uint32_t cw[RHO];
-  int ck = -1, cwk = -1;
-  int cnt = 0;
-  int32_t* out = nullptr;
-  int seg_len = 0;
-  if (EMIT) {
-    out = a.paths + 2 * (a.path_base[pd.out] + a.seg_off[item]);
-    seg_len = a.seg_len[item];
+  int2* runs = a.runs + (int64_t)pd.out * a.L + i0;
+  bool ok = jx >= 0 && jx < pd.N && jtop >= 0 && jtop <= jx;
+  if (ok) {
+    Walk st{iend - i0, jx, jx, -1};
+    const WalkEnd end = walk_strip<RHO>(st, 0, runs, [&](int b, int k, int r, uint32_t& nl, uint32_t& dd) {
+      const uint32_t* p = codes + ((int64_t)b * 2 * RHO + r) * kWave + k;
+      dd = p[0];
+      nl = dd | p[RHO * kWave];
+    });
+    ok = end == kWalkDone && st.jtop == jtop;
   }
-  while (!bad) {
-    if (i < i0 || j < 0 || (EMIT && cnt >= seg_len)) {   // left the strip: inconsistent tags
-      if (lane == 0) atomicOr(a.status, kStatusBadPath);
-      bad = true;
-      break;
-    }
-    if (EMIT && lane == 0) {
-      out[2 * (seg_len - 1 - cnt)] = i;
-      out[2 * (seg_len - 1 - cnt) + 1] = j;
-    }
-    ++cnt;
-    if (i == i0 && j == jstop) {
-      if (!EMIT && lane == 0) { run_lo[0] = j; run_hi[0] = hi; }
-      break;
-    }
-    const int q = i - i0;
-    const int k = q / RHO, r = q - k * RHO;
-    const int t = j + k;
-    const int w = t >> 4;
-    if (k != ck || w != cwk) {   // the RHO words of (lane k, word w) into registers
-      if (w < wlo || w > whi) {
-        __syncthreads();
-        wlo = max(0, w - kWalkWords + 1);
-        whi = w;
-        for (int ww = wlo; ww <= whi; ++ww)
-#pragma unroll
-          for (int rr = 0; rr < RHO; ++rr)
-            blk[ww - wlo][rr][lane] = codes[((int64_t)ww * RHO + rr) * kWave + lane];
-        __syncthreads();
-      }
-#pragma unroll
-      for (int rr = 0; rr < RHO; ++rr) cw[rr] = blk[w - wlo][rr][k];
-      ck = k;
-      cwk = w;
-    }
-    uint32_t word = cw[0];
-#pragma unroll
-    for (int rr = 1; rr < RHO; ++rr) word = r == rr ? cw[rr] : word;
-    // step u of a word: bit 31-2u = diagonal chosen, bit 30-2u = up chosen
-    const int u = t & 15;
-    const uint32_t code = (word >> (30 - 2 * u)) & 3u;
-    if (code == 0u) {   // left
-      --j;
-      if (!EMIT && u > 0) {
-        // the cells (i, j), (i, j-1), ... of this word that are left moves
-        // too: their fields (steps u-1, u-2, ...) sit above this one
-        const uint32_t rest = word >> (32 - 2 * u);
-        int more = rest == 0u ? u : (int)(__builtin_ctz(rest) >> 1);
-        if (i == i0) more = min(more, j - jstop);   // the run ends at the entry cell
-        j -= more;
-        cnt += more;
-      }
-    } else {
-      if (!EMIT && lane == 0) { run_lo[q] = j; run_hi[q] = hi; }
-      --i;
-      if (code & 2u) --j;   // diagonal
-      hi = j;
-    }
-  }
-  if (EMIT) return;
-  if (lane == 0) a.seg_len[item] = bad ? 0 : cnt;
-  if (a.psum == nullptr) return;
-  __syncthreads();
-  const TY* __restrict__ Y = static_cast<const TY*>(a.y);
-  const int nrows = iend - i0 + 1;
-  for (int q = lane; q < nrows; q += kWave) {
-    const int lo = bad ? 0 : run_lo[q], h = bad ? -1 : run_hi[q];
-    const int64_t o = ((int64_t)pd.out * a.L + i0 + q);
-#pragma unroll
-    for (int c = 0; c < D; ++c) {
-      double acc = 0.0;
-      for (int jj = h; jj >= lo; --jj) acc = acc + static_cast<double>(Y[(pd.y_off + jj) * D + c]);
-      a.psum[o * D + c] = acc;
-    }
-    a.pcnt[o] = h - lo + 1;
+  if (!ok) {
+    if (lane == 0) atomicOr(a.status, kStatusBadPath);
+    for (int q = lane; q <= iend - i0; q += kWave) runs[q] = make_int2(0, -1);
   }
 }
 
-// Path recovery, one pair per workgroup.  From (M-1, N-1) the walk follows
-// the argmin codes strip by strip, the bottom strip first: in each strip
-// from the column where the path crosses the strip's bottom row up to the
-// cell of its top row whose code leaves the strip (an up or diagonal move
-// out of row i0), which gives the column where the path crosses the bottom
-// row of the strip above.  Per strip it records the segment (bottom-row
-// column, top-row column) and its length, for the path list, and per row
-// the run of columns [lo, hi] the path occupies (for the DBA sums, which
-// run_sum_kernel forms in parallel).  All 64 lanes walk in lockstep
-// (identical state): the code-word staging is cooperative, and the words
-// read back from LDS are moved to scalar registers, so the walk itself runs
-// on the scalar unit.  A walk that leaves its strip marks the status word,
-// and every strip from there up gets empty runs.
-template <int RHO>
-__global__ __launch_bounds__(kWave) void path_walk_kernel(WalkArgs a) {
-  constexpr int H = kWave * RHO;
-  __shared__ uint32_t blk[kWalkWords][RHO][kWave];
-  const int lane = threadIdx.x;
-  if (skipped(a.skip)) return;
-  const PairDesc pd = a.pairs[blockIdx.x];
-  int2* runs = a.runs ? a.runs + (int64_t)pd.out * a.L : nullptr;   // null: no DBA sums wanted
-  bool bad = false;
-  int jx = pd.N - 1;   // where the path crosses the current strip's bottom row
-  for (int s = pd.S - 1; s >= 0; --s) {
-    const int item = pd.item_base + s;
-    const int i0 = s * H;
-    const int iend = min(pd.M, i0 + H) - 1;
-    const uint32_t* codes = a.codes + pd.code_base + (int64_t)s * pd.WT * RHO * kWave;
-    if (jx < 0 || jx >= pd.N) bad = true;
-    int i = iend, j = jx, hi = jx, jtop = -1, jnext = -1, cnt = 0;
-    int k = (iend - i0) / RHO, r = (iend - i0) - k * RHO;   // lane and row of row i
-    int wlo = 1 << 30, whi = -1;
-    uint32_t cw[RHO];
-    int ck = -1, cwk = -1;
-    while (!bad) {
-      if (j < 0) {   // walked out of the strip: inconsistent codes
-        bad = true;
-        break;
-      }
-      ++cnt;
-      const int t = j + k;
-      const int w = t >> 4;
-      if (k != ck || w != cwk) {   // the RHO words of (lane k, word w) into registers
-        if (w < wlo || w > whi) {
-          __syncthreads();
-          wlo = max(0, w - kWalkWords + 1);
-          whi = w;
-          for (int ww = wlo; ww <= whi; ++ww)
-#pragma unroll
-            for (int rr = 0; rr < RHO; ++rr)
-              blk[ww - wlo][rr][lane] = codes[((int64_t)ww * RHO + rr) * kWave + lane];
-          __syncthreads();
-        }
-        // the same words in every lane: scalar registers, so the walk's
-        // arithmetic and branches below stay on the scalar unit
-#pragma unroll
-        for (int rr = 0; rr < RHO; ++rr) cw[rr] = __builtin_amdgcn_readfirstlane(blk[w - wlo][rr][k]);
-        ck = k;
-        cwk = w;
-      }
-      uint32_t word = cw[0];
-#pragma unroll
-      for (int rr = 1; rr < RHO; ++rr) word = r == rr ? cw[rr] : word;
-      // step u of a word: bit 31-2u = diagonal chosen, bit 30-2u = up chosen
-      const int u = t & 15;
-      const uint32_t code = (word >> (30 - 2 * u)) & 3u;
-      if (code == 0u) {   // left
-        --j;
-        if (u > 0) {
-          // the cells (i, j), (i, j-1), ... of this word that are left moves
-          // too: their fields (steps u-1, u-2, ...) sit above this one
-          const uint32_t rest = word >> (32 - 2 * u);
-          const int more = rest == 0u ? u : (int)(__builtin_ctz(rest) >> 1);
-          j -= more;
-          cnt += more;
-        }
-      } else {
-        if (runs && lane == 0) runs[i] = make_int2(j, hi);
-        if (i == i0) {   // the move out of the strip
-          jtop = j;
-          jnext = j - ((code & 2u) ? 1 : 0);
-          break;
-        }
-        --i;
-        if (--r < 0) {
-          r = RHO - 1;
-          --k;
-        }
-        if (code & 2u) --j;   // diagonal
-        hi = j;
-      }
-    }
-    if (bad) {
-      if (lane == 0) atomicOr(a.status, kStatusBadPath);
-      if (runs)
-        for (int q = i0 + lane; q <= iend; q += kWave) runs[q] = make_int2(0, -1);
-    }
-    if (lane == 0) {
-      a.seg_out[item] = bad ? make_int2(-1, -1) : make_int2(jx, jtop);
-      a.seg_len[item] = bad ? 0 : cnt;
-    }
-    if (s > 0 && !bad && jnext < 0) bad = true;   // the path left row 0 before strip 0
-    jx = jnext;
-  }
-}
-
-// Per (cycle, barycenter row): the sum of the cycle's samples over the run
-// [lo, hi] of the row's path, in descending column order, and its length.
+// The DBA update from the row runs: per cycle and row the sum of the cycle's
+// samples over the run [lo, hi] in descending column order, folded over the
+// cycles in ascending order with their weights, and the mean.  A workgroup
+// takes kFoldRows rows and kFoldCycles cycles at a time: each thread sums one
+// (cycle, row) run, then one thread per (row, channel) folds the sums from
+// LDS in order, so no per-cycle sums go through memory.
+constexpr int kFoldRows = 16, kFoldCycles = 16;
 template <typename TY, int D>
-__global__ void run_sum_kernel(const int2* __restrict__ runs, const int64_t* __restrict__ off,
-                               const void* y, int n, int64_t L, double* __restrict__ psum,
-                               int* __restrict__ pcnt, const int* skip) {
+__global__ __launch_bounds__(kFoldRows * kFoldCycles)
+void run_fold_kernel(const int2* __restrict__ runs, const int64_t* __restrict__ off, const void* y,
+                     const double* __restrict__ w, int n, int64_t L, double* __restrict__ bout,
+                     int64_t* __restrict__ counts, const int* skip) {
+  __shared__ double ps[kFoldCycles][D][kFoldRows];
+  __shared__ int pc[kFoldCycles][kFoldRows];
   if (skipped(skip)) return;
   const TY* __restrict__ Y = static_cast<const TY*>(y);
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t o = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; o < (int64_t)n * L; o += stride) {
-    const int2 rn = runs[o];
-    const int64_t base = off[o / L];
+  const int q = threadIdx.x / kFoldRows, row = threadIdx.x % kFoldRows;
+  const int64_t l = blockIdx.x * (int64_t)kFoldRows + row;
+  const int fc = threadIdx.x / kFoldRows;   // the channel this thread folds (fc < D)
+  double S = 0.0, C = 0.0;
+  int64_t K = 0;
+  for (int p0 = 0; p0 < n; p0 += kFoldCycles) {
+    const int p = p0 + q;
+    if (p < n && l < L) {
+      const int2 rn = runs[(int64_t)p * L + l];
+      const int64_t base = off[p];
+      double acc[D];
 #pragma unroll
-    for (int c = 0; c < D; ++c) {
-      double acc = 0.0;
-      for (int jj = rn.y; jj >= rn.x; --jj) acc = acc + static_cast<double>(Y[(base + jj) * D + c]);
-      psum[o * D + c] = acc;
+      for (int c = 0; c < D; ++c) acc[c] = 0.0;
+      for (int jj = rn.y; jj >= rn.x; --jj) {
+#pragma unroll
+        for (int c = 0; c < D; ++c) acc[c] = acc[c] + static_cast<double>(Y[(base + jj) * D + c]);
+      }
+#pragma unroll
+      for (int c = 0; c < D; ++c) ps[q][c][row] = acc[c];
+      pc[q][row] = rn.y - rn.x + 1;
     }
-    pcnt[o] = rn.y - rn.x + 1;
+    __syncthreads();
+    if (fc < D && l < L) {
+      const int m = min(kFoldCycles, n - p0);
+      for (int e = 0; e < m; ++e) {
+        const double wp = w ? w[p0 + e] : 1.0;
+        const int k = pc[e][row];
+        S = S + wp * ps[e][fc][row];
+        C = C + wp * (double)k;
+        K += k;
+      }
+    }
+    __syncthreads();
+  }
+  if (fc < D && l < L) {
+    bout[l * D + fc] = S / C;
+    if (fc == 0) counts[l] = K;
   }
 }
 
@@ -309,43 +152,46 @@ __global__ void fill_sent_kernel(unsigned long long* r, int64_t nr, int* x, int6
     x[k] = kSentX;
 }
 
-// Segment offsets in forward path order (strip 0 first) and |pi| per pair.
-__global__ void seg_prefix_kernel(const PairDesc* __restrict__ pairs, int n_pairs,
-                                  const int* __restrict__ seg_len, int* __restrict__ seg_off,
-                                  int64_t* __restrict__ path_len) {
-  const int p = blockIdx.x * blockDim.x + threadIdx.x;
-  if (p >= n_pairs) return;
-  const PairDesc pd = pairs[p];
-  int off = 0;
-  for (int s = 0; s < pd.S; ++s) {
-    seg_off[pd.item_base + s] = off;
-    off += seg_len[pd.item_base + s];
+// The path list of every pair from its row runs, and its length: a scan of
+// the run lengths over the rows gives each row's place.  One workgroup per
+// pair.
+constexpr int kEmitThreads = 256;
+__global__ __launch_bounds__(kEmitThreads)
+void emit_kernel(const int2* __restrict__ runs, const int64_t* __restrict__ path_base, int64_t L,
+                 int32_t* __restrict__ paths, int64_t* __restrict__ path_len, const int* skip) {
+  __shared__ int part[kEmitThreads / kWave];
+  if (skipped(skip)) return;
+  const int pair = blockIdx.x, lane = threadIdx.x % kWave, wv = threadIdx.x / kWave;
+  const int2* rn = runs + (int64_t)pair * L;
+  int32_t* out = paths + 2 * path_base[pair];
+  int64_t done = 0;
+  for (int64_t i0 = 0; i0 < L; i0 += kEmitThreads) {
+    const int64_t i = i0 + threadIdx.x;
+    const int2 r = i < L ? rn[i] : make_int2(0, -1);
+    const int len = r.y - r.x + 1;
+    int inc = len;   // inclusive scan over the wave
+#pragma unroll
+    for (int d = 1; d < kWave; d <<= 1) {
+      const int v = __shfl_up(inc, d);
+      if (lane >= d) inc += v;
+    }
+    if (lane == kWave - 1) part[wv] = inc;
+    __syncthreads();
+    int before = 0, all = 0;
+#pragma unroll
+    for (int q = 0; q < kEmitThreads / kWave; ++q) {
+      if (q < wv) before += part[q];
+      all += part[q];
+    }
+    int64_t at = done + before + inc - len;
+    for (int j = r.x; j <= r.y; ++j, ++at) {
+      out[2 * at] = (int)i;
+      out[2 * at + 1] = j;
+    }
+    done += all;
+    __syncthreads();
   }
-  if (path_len) path_len[pd.out] = off;
-}
-
-// B'_l = S_l / C_l with S_l, C_l folded over cycles in ascending order.
-__global__ void dba_reduce_kernel(const double* __restrict__ psum, const int* __restrict__ pcnt,
-                                  const double* __restrict__ w, int n, int64_t L, int d,
-                                  double* __restrict__ bout, int64_t* __restrict__ counts) {
-  const int64_t idx = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (idx >= L * d) return;
-  const int64_t l = idx / d;
-  const int c = (int)(idx - l * d);
-  double S = 0.0, C = 0.0;
-  int64_t K = 0;
-  for (int p = 0; p < n; ++p) {
-    const double wp = w ? w[p] : 1.0;
-    S = S + wp * psum[((int64_t)p * L + l) * d + c];
-  }
-  for (int p = 0; p < n; ++p) {
-    const double wp = w ? w[p] : 1.0;
-    const int k = pcnt[(int64_t)p * L + l];
-    C = C + wp * (double)k;
-    K += k;
-  }
-  bout[idx] = S / C;
-  if (c == 0 && counts) counts[l] = K;
+  if (threadIdx.x == 0) path_len[pair] = done;
 }
 
 __global__ void score_kernel(const double* __restrict__ dist, const int* __restrict__ len, int n,
@@ -431,24 +277,12 @@ hipError_t launch_fwd(int d, int rho, int mode, bool euc, bool x_is_cycle, int y
   return launch_fwd_impl<double>(d, rho, mode, euc, x_is_cycle, ydtype, a, grid, st);
 }
 
-template <typename TY, int D, int RHO>
-static hipError_t launch_walk_t(bool emit, const WalkArgs& a, int n_items, hipStream_t st) {
-  if (emit)
-    hipLaunchKernelGGL((walk_kernel<TY, D, RHO, true>), dim3(n_items), dim3(kWave), 0, st, a);
-  else
-    hipLaunchKernelGGL((walk_kernel<TY, D, RHO, false>), dim3(n_items), dim3(kWave), 0, st, a);
+hipError_t launch_walk(int rho, const WalkArgs& a, int n_items, hipStream_t st) {
+  if (rho == 4) hipLaunchKernelGGL(walk_kernel<4>, dim3(n_items), dim3(kWave), 0, st, a);
+  else if (rho == 2) hipLaunchKernelGGL(walk_kernel<2>, dim3(n_items), dim3(kWave), 0, st, a);
+  else if (rho == 5) hipLaunchKernelGGL(walk_kernel<5>, dim3(n_items), dim3(kWave), 0, st, a);
+  else return hipErrorInvalidValue;
   return hipGetLastError();
-}
-
-hipError_t launch_walk(int d, int rho, int ydtype, bool emit, const WalkArgs& a, int n_items,
-                       hipStream_t st) {
-#define CALLW(D, R) (ydtype == 0 ? launch_walk_t<float, D, R>(emit, a, n_items, st) \
-                                 : launch_walk_t<double, D, R>(emit, a, n_items, st))
-  if (rho == 4) { WTS_D_SWITCH(d, 4, CALLW) }
-  if (rho == 2) { WTS_D_SWITCH(d, 2, CALLW) }
-  if (rho == 5) { WTS_D_SWITCH(d, 5, CALLW) }
-#undef CALLW
-  return hipErrorInvalidValue;
 }
 
 hipError_t launch_chain(const PairDesc* pairs, int n_pairs, const int* bnd_aux,
@@ -459,35 +293,30 @@ hipError_t launch_chain(const PairDesc* pairs, int n_pairs, const int* bnd_aux,
   return hipGetLastError();
 }
 
-hipError_t launch_path_walk(int rho, const WalkArgs& a, int n_pairs, hipStream_t st) {
-  if (n_pairs <= 0) return hipSuccess;
-  if (rho == 4) hipLaunchKernelGGL(path_walk_kernel<4>, dim3(n_pairs), dim3(kWave), 0, st, a);
-  else if (rho == 2) hipLaunchKernelGGL(path_walk_kernel<2>, dim3(n_pairs), dim3(kWave), 0, st, a);
-  else if (rho == 5) hipLaunchKernelGGL(path_walk_kernel<5>, dim3(n_pairs), dim3(kWave), 0, st, a);
-  else return hipErrorInvalidValue;
-  return hipGetLastError();
-}
-
 template <typename TY, int D>
-static hipError_t launch_run_sum_t(const int2* runs, const int64_t* off, const void* y, int n,
-                                   int64_t L, double* psum, int* pcnt, const int* skip,
-                                   hipStream_t st) {
-  const int64_t rows = (int64_t)n * L;
-  const unsigned blocks = (unsigned)std::min<int64_t>((rows + 255) / 256, 65536);
-  hipLaunchKernelGGL((run_sum_kernel<TY, D>), dim3(blocks), dim3(256), 0, st, runs, off, y, n, L,
-                     psum, pcnt, skip);
+static hipError_t launch_run_fold_t(const int2* runs, const int64_t* off, const void* y,
+                                    const double* w, int n, int64_t L, double* bout,
+                                    int64_t* counts, const int* skip, hipStream_t st) {
+  hipLaunchKernelGGL((run_fold_kernel<TY, D>), dim3((unsigned)((L + kFoldRows - 1) / kFoldRows)),
+                     dim3(kFoldRows * kFoldCycles), 0, st, runs, off, y, w, n, L, bout, counts, skip);
   return hipGetLastError();
 }
 
-hipError_t launch_run_sum(int d, int ydtype, const int2* runs, const int64_t* off, const void* y,
-                          int n, int64_t L, double* psum, int* pcnt, const int* skip,
-                          hipStream_t st) {
-  if ((int64_t)n * L <= 0) return hipSuccess;
-#define CALLS(D, R) (ydtype == 0 ? launch_run_sum_t<float, D>(runs, off, y, n, L, psum, pcnt, skip, st) \
-                                 : launch_run_sum_t<double, D>(runs, off, y, n, L, psum, pcnt, skip, st))
+hipError_t launch_run_fold(int d, int ydtype, const int2* runs, const int64_t* off, const void* y,
+                           const double* w, int n, int64_t L, double* bout, int64_t* counts,
+                           const int* skip, hipStream_t st) {
+#define CALLS(D, R) (ydtype == 0 ? launch_run_fold_t<float, D>(runs, off, y, w, n, L, bout, counts, skip, st) \
+                                 : launch_run_fold_t<double, D>(runs, off, y, w, n, L, bout, counts, skip, st))
   WTS_D_SWITCH(d, 0, CALLS)
 #undef CALLS
   return hipErrorInvalidValue;
+}
+
+hipError_t launch_emit(const int2* runs, const int64_t* path_base, int n, int64_t L,
+                       int32_t* paths, int64_t* path_len, const int* skip, hipStream_t st) {
+  hipLaunchKernelGGL(emit_kernel, dim3((unsigned)n), dim3(kEmitThreads), 0, st, runs, path_base, L,
+                     paths, path_len, skip);
+  return hipGetLastError();
 }
 
 hipError_t launch_zero(int* p, int64_t n, hipStream_t st) {
@@ -504,21 +333,6 @@ hipError_t launch_fill_sentinels(double* r, int64_t nr, int* x, int64_t nx, hipS
   const int64_t blocks = (n + 255) / 256;
   hipLaunchKernelGGL(fill_sent_kernel, dim3((unsigned)(blocks < 8192 ? blocks : 8192)), dim3(256), 0,
                      st, reinterpret_cast<unsigned long long*>(r), nr, x, nx);
-  return hipGetLastError();
-}
-
-hipError_t launch_seg_prefix(const PairDesc* pairs, int n_pairs, const int* seg_len,
-                             int* seg_off, int64_t* path_len, hipStream_t st) {
-  hipLaunchKernelGGL(seg_prefix_kernel, dim3((n_pairs + 63) / 64), dim3(64), 0, st, pairs,
-                     n_pairs, seg_len, seg_off, path_len);
-  return hipGetLastError();
-}
-
-hipError_t launch_dba_reduce(const double* psum, const int* pcnt, const double* w, int n,
-                             int64_t L, int d, double* bout, int64_t* counts, hipStream_t st) {
-  const int64_t tot = L * d;
-  hipLaunchKernelGGL(dba_reduce_kernel, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, st,
-                     psum, pcnt, w, n, L, d, bout, counts);
   return hipGetLastError();
 }
 

@@ -1,4 +1,4 @@
-// wts_kernels.h -- host-side launchers of the WETSAND kernels (wts_dtw.hip).
+// wts_kernels.h -- host-side launchers of the WETSAND kernels.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -7,23 +7,27 @@
 
 namespace wts {
 
-struct WalkArgs {
+struct WalkArgs {           // path recovery by strips (after a PATHT sweep)
   const PairDesc* pairs;
   const int2* items;
   const int2* seg;          // per item: (bottom-row column, top-row column) of the path
-  int2* seg_out;            // the same, written by the path walk
   int2* runs;               // [out][L]: the columns [lo, hi] of each row's path run
   const uint32_t* codes;
-  const void* y;
-  double* psum;             // [out][L][d] per-cycle row sums, or nullptr
-  int* pcnt;                // [out][L] per-cycle row counts
   int64_t L;
-  int* seg_len;             // per item: cells of the path inside the strip
-  const int* seg_off;       // per item: offset of the strip's segment in the pair's path
-  const int64_t* path_base; // per pair slot: first path row
-  int32_t* paths;           // [rows][2]
   int* status;              // device status word
   const int* skip;          // validation flag of the call (or null)
+};
+
+struct TraceArgs {          // path recovery from checkpoints (after a CKPT sweep)
+  const PairDesc* pairs;
+  const void* x;            // barycenter rows (float64)
+  const void* y;            // cycle values
+  const double* states;     // the sweep's checkpoints (see FwdArgs)
+  const double* bnd_r;      // the sweep's strip rows
+  int2* runs;               // [out][L]: the columns [lo, hi] of each row's path run
+  int64_t L;
+  int* status;
+  const int* skip;
 };
 
 // fp32: the float32-decision instances (float32 cycles, squared cost only).
@@ -32,26 +36,25 @@ hipError_t launch_fwd(int d, int rho, int mode, bool euc, bool x_is_cycle, int y
 hipError_t launch_fwd32(int d, int rho, int mode, bool euc, bool x_is_cycle, int ydtype,
                         const FwdArgs& a, int grid, hipStream_t st);
 // Path recovery after a PATHT sweep: the strip chain (segments from the
-// entry tags), then walks of all strips at once (emit = false: row runs,
-// segment lengths and DBA partial sums; emit = true: the path list).
-hipError_t launch_walk(int d, int rho, int ydtype, bool emit, const WalkArgs& a, int n_items,
-                       hipStream_t st);
+// entry tags), then walks of all strips at once (row runs).
+hipError_t launch_walk(int rho, const WalkArgs& a, int n_items, hipStream_t st);
 hipError_t launch_chain(const PairDesc* pairs, int n_pairs, const int* bnd_aux,
                         const int* out_aux, int2* seg, int* status, const int* skip,
                         hipStream_t st);
-// Path recovery after a PATH sweep: one workgroup per pair walks its strips
-// in turn (segments, their lengths, the row runs).
-hipError_t launch_path_walk(int rho, const WalkArgs& a, int n_pairs, hipStream_t st);
-// DBA partial sums per (cycle, barycenter row) from the pair walk's runs.
-hipError_t launch_run_sum(int d, int ydtype, const int2* runs, const int64_t* off, const void* y,
-                          int n, int64_t L, double* psum, int* pcnt, const int* skip,
+// Path recovery after a CKPT sweep: one workgroup per pair (row runs).
+hipError_t launch_trace(int d, int rho, int ydtype, bool fp32, const TraceArgs& a, int n_pairs,
+                        hipStream_t st);
+hipError_t launch_trace32(int d, int rho, int ydtype, const TraceArgs& a, int n_pairs,
                           hipStream_t st);
+// The DBA update from the row runs: sums, counts and means.
+hipError_t launch_run_fold(int d, int ydtype, const int2* runs, const int64_t* off, const void* y,
+                           const double* w, int n, int64_t L, double* bout, int64_t* counts,
+                           const int* skip, hipStream_t st);
+// The path lists and their lengths from the row runs.
+hipError_t launch_emit(const int2* runs, const int64_t* path_base, int n, int64_t L,
+                       int32_t* paths, int64_t* path_len, const int* skip, hipStream_t st);
 hipError_t launch_zero(int* p, int64_t n, hipStream_t st);
 hipError_t launch_fill_sentinels(double* r, int64_t nr, int* x, int64_t nx, hipStream_t st);
-hipError_t launch_seg_prefix(const PairDesc* pairs, int n_pairs, const int* seg_len,
-                             int* seg_off, int64_t* path_len, hipStream_t st);
-hipError_t launch_dba_reduce(const double* psum, const int* pcnt, const double* w, int n,
-                             int64_t L, int d, double* bout, int64_t* counts, hipStream_t st);
 hipError_t launch_score(const double* dist, const int* len, int n, double* score,
                         int64_t* path_len, hipStream_t st);
 hipError_t launch_sub_out(const int* start, const int* end, int n, int64_t* a_star,

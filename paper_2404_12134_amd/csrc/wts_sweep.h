@@ -1,5 +1,5 @@
 // wts_sweep.h -- the DTW wavefront sweep of gfx950 (value, value + path
-// length, argmin codes, Sub-DTW) and its launchers, shared by the float64
+// length, checkpoints, argmin codes, Sub-DTW) and its launchers, shared by the float64
 // instances (wts_dtw.hip) and the float32-decision instances (wts_dtw32.hip).
 //
 // The recurrence (Eq. 5 with gamma = 0, i.e. Eq. 1 by dynamic programming):
@@ -110,9 +110,9 @@ __global__ __launch_bounds__(kWave * kSweepWaves, MODE == MODE_DIST && D <= 4 ? 
 void dtw_fwd_kernel(FwdArgs a) {
   constexpr int H = kWave * RHO;
   // tags carried along the argmin: the path length (DIST_LEN), the start
-  // column (SUB) or the strip entry (PATHT); PATH keeps only its codes
+  // column (SUB) or the strip entry (PATHT)
   constexpr bool kAux = MODE == MODE_DIST_LEN || MODE == MODE_SUB || MODE == MODE_PATHT;
-  constexpr bool kCodes = MODE == MODE_PATH || MODE == MODE_PATHT;
+  constexpr bool kCodes = MODE == MODE_PATHT;
   // Y ring; slots kRing .. kRing+15 mirror slots 0 .. 15, so a group of 16
   // steps reads consecutive slots from one base without wrapping
   static_assert(!EUC || sizeof(TC) == 8, "the l2 cost is evaluated in float64 only");
@@ -174,9 +174,9 @@ void dtw_fwd_kernel(FwdArgs a) {
     }
     TC left[RHO];
     int lx[RHO];
-    uint32_t acc[RHO];
+    uint32_t accd[RHO], accu[RHO];   // code planes: diagonal chosen; up not above left
 #pragma unroll
-    for (int r = 0; r < RHO; ++r) { left[r] = INF; lx[r] = 0; acc[r] = 0u; }
+    for (int r = 0; r < RHO; ++r) { left[r] = INF; lx[r] = 0; accd[r] = accu[r] = 0u; }
     TC upprev = (s == 0 && lane == 0) ? (TC)0 : INF;   // r(-1,-1) = 0 at the origin
     // Sub-DTW: running minimum of the last row (lowest column on ties)
     const bool last_strip = s + 1 == pd.S;
@@ -230,16 +230,20 @@ void dtw_fwd_kernel(FwdArgs a) {
     };
     // Stores of group tg: lane 63's bottom row (columns tg-63 .. tg-48, at
     // indices tg .. tg+15 of the strip's row, by lanes 0..15 in one
-    // coalesced store) and, for PATH, the group's argmin code words.
+    // coalesced store) and, for PATHT, every second group, the code words of
+    // its 32 steps (the first step in the top bit).
     auto publish = [&](int tg) {
       const int j = tg - 63 + lane;
       const bool w = has_next && lane < 16 && j >= 0 && j < N;
       st_dev(rr_out, w ? (tg + lane) * kB : kDrop, stg_r[lane & 15]);
       if (kAux) st_dev(rx_out, w ? (tg + lane) * 4 : kDrop, stg_x[lane & 15]);
-      if (kCodes) {
-        const int64_t cw = pd.code_base + (int64_t)(s * pd.WT + (tg >> 4)) * RHO * kWave + lane;
+      if (kCodes && (tg & 16)) {
+        uint32_t* cw = a.codes + pd.code_base + (int64_t)(s * pd.WT + ((tg >> 4) - 1)) * RHO * kWave + lane;
 #pragma unroll
-        for (int r = 0; r < RHO; ++r) a.codes[cw + r * kWave] = acc[r];
+        for (int r = 0; r < RHO; ++r) {
+          cw[r * kWave] = accd[r];
+          cw[(RHO + r) * kWave] = accu[r];
+        }
       }
     };
     fetch(0);
@@ -266,6 +270,13 @@ void dtw_fwd_kernel(FwdArgs a) {
     for (int t0 = 0; t0 < Tend; t0 += kChunk) {
       const int tcnt = min(kChunk, Tend - t0);
       const bool more = t0 + kChunk < Tend;
+      if (MODE == MODE_CKPT) {   // the sweep state at the start of these 64 steps
+        TC* p = reinterpret_cast<TC*>(a.states) + pd.state_base +
+                ((int64_t)s * ((pd.WT + 3) >> 2) + t0 / kChunk) * (RHO + 1) * kWave + lane;
+#pragma unroll
+        for (int r = 0; r < RHO; ++r) p[r * kWave] = left[r];
+        p[RHO * kWave] = upprev;
+      }
       if (more) {   // next chunk of Y into registers; stored to LDS after this sweep
         const int j = t0 + kChunk + lane;
         const int64_t row = (pd.y_off + min(j, N - 1)) * D;
@@ -323,7 +334,7 @@ void dtw_fwd_kernel(FwdArgs a) {
           const TC dg0 = upprev;
           upprev = upin;
           upprevx = upinx;
-          bool isd_r[RHO], isu_r[RHO];   // argmin of each row's cell (PATH, PATHT)
+          bool isd_r[RHO], isu_r[RHO];   // argmin of each row's cell (PATHT)
 #pragma unroll
           for (int r = 0; r < RHO; ++r) { isd_r[r] = false; isu_r[r] = false; }
           if (FULL || (j >= 0 && j < N)) {
@@ -338,7 +349,7 @@ void dtw_fwd_kernel(FwdArgs a) {
               if constexpr (EUC) delta = __builtin_sqrt(delta);
               const TC rv = delta + m;
               int rxv = 0;
-              if (MODE != MODE_DIST) {
+              if (kAux || kCodes) {
                 const bool isd = dg <= m1;
                 const bool isu = up <= lf;
                 if (kAux) {
@@ -374,10 +385,13 @@ void dtw_fwd_kernel(FwdArgs a) {
             }
           }
           if (kCodes) {
-            // every step of every lane shifts two bits into the row's code
-            // word (cells outside the grid shift in don't-care bits)
+            // every step of every lane shifts a bit into each of the row's
+            // code words (cells outside the grid shift in zeros)
 #pragma unroll
-            for (int r = 0; r < RHO; ++r) acc[r] = push_bit(push_bit(acc[r], isd_r[r]), isu_r[r]);
+            for (int r = 0; r < RHO; ++r) {
+              accd[r] = push_bit(accd[r], isd_r[r]);
+              accu[r] = push_bit(accu[r], isu_r[r]);
+            }
           }
           stg_r[sb + u] = bot;   // staged in LDS, stored at the next group's start
           if (kAux) stg_x[sb + u] = botx;
@@ -468,7 +482,7 @@ hipError_t launch_one(const FwdArgs& a, int grid, hipStream_t st) {
 template <typename TX, typename TY, typename TC, int D, int RHO>
 hipError_t launch_fwd_t(int mode, bool euc, const FwdArgs& a, int grid, hipStream_t st) {
   if (mode == MODE_DIST) return launch_one<TX, TY, TC, D, RHO, MODE_DIST, false>(a, grid, st);
-  if (mode == MODE_PATH) return launch_one<TX, TY, TC, D, RHO, MODE_PATH, false>(a, grid, st);
+  if (mode == MODE_CKPT) return launch_one<TX, TY, TC, D, RHO, MODE_CKPT, false>(a, grid, st);
   if (mode == MODE_PATHT) return launch_one<TX, TY, TC, D, RHO, MODE_PATHT, false>(a, grid, st);
   if (mode == MODE_SUB) {
     if (euc) return hipErrorInvalidValue;

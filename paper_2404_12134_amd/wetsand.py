@@ -168,9 +168,9 @@ class Plan:
     the longer length (Table I).  dense_e=True makes the Soft-DTW backward
     sweep every tile, also those whose E entries are exactly zero (same
     results, more time).  walk picks the path recovery of the DBA and
-    path calls: "strips" (entry tags, all strips walked at once), "pairs"
-    (no tags, each pair walks its strips in turn) or "auto" (the library
-    decides by the batch's size); the results are the same bits."""
+    path calls: "strips" (codes and entry tags, all strips walked at once),
+    "pairs" (checkpoints, each pair walks its strips in turn) or "auto" (the
+    library decides by the batch's size); the results are the same bits."""
 
     def __init__(self, offsets, d: int, dtype: str, L: int, device: int = 0, cost: str = "sq",
                  rho: int = 0, grid: int = 0, band: float = 0.0, validate: bool = False,
