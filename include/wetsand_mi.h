@@ -109,11 +109,13 @@ enum { WTS_WALK_AUTO = 0, WTS_WALK_STRIPS = 1, WTS_WALK_PAIRS = 2 };
 typedef struct {
   int32_t cost;       /* WTS_COST_* for wts_dtw_align / wts_anomaly_score; DBA, Soft-DTW and
                          the medoid always use the squared cost                              */
-  int32_t rho;        /* rows per lane in the wavefront sweeps: 0 = automatic (4, or 5 for
-                         barycenter plans whose strips would just about fill every SIMD);
-                         2, 4 or 5 for any plan (Soft-DTW sweeps always use 2); other
-                         values return WTS_E_UNSUPPORTED                                     */
-  int32_t grid;       /* workgroups of the persistent sweep (0 = tuned default)              */
+  int32_t rho;        /* rows per lane in the wavefront sweeps: 0 = automatic (2 for barycenter
+                         plans of few strips, which teams of four waves a strip sweep; 4, or 5
+                         where that balances the strips better, else); 2, 4 or 5 for any plan
+                         (Soft-DTW sweeps always use 2); other values return
+                         WTS_E_UNSUPPORTED                                                   */
+  int32_t grid;       /* waves of the persistent one-wave-a-strip sweep (0 = tuned default, and
+                         batches of few strips are swept by teams)                          */
   int32_t validate;   /* 1: every compute call first checks its inputs for NaN / infinity on
                          the device (see Conventions); 0: no check                           */
   int32_t decision;   /* precision of the hard-DTW sweeps (wts_dtw_align, wts_dba_iterate,

@@ -23,6 +23,8 @@ OBJDIR = os.path.join(HERE, "_build")
 # The Soft-DTW kernels never subtract two infinities: every computed cell has
 # at least one finite predecessor, so the same holds there.
 SOURCES = {"wts_dtw.hip": ["-fno-honor-nans"], "wts_dtw32.hip": ["-fno-honor-nans"],
+           "wts_team2.hip": ["-fno-honor-nans"], "wts_team4.hip": ["-fno-honor-nans"],
+           "wts_team32.hip": ["-fno-honor-nans"],
            "wts_trace.hip": ["-fno-honor-nans"], "wts_trace32.hip": ["-fno-honor-nans"],
            "wts_soft.hip": ["-fno-honor-nans"], "wts_abi.hip": [], "wts_aux.hip": []}
 ARCH = os.environ.get("WTS_OFFLOAD_ARCH", "gfx950")

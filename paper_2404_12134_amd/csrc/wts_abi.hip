@@ -58,6 +58,7 @@ struct PairSet {
   int64_t code_words = 0, bnd_elems = 0, aux_strip_elems = 0, state_elems = 0, row_elems = 0;
   int64_t max_rows = 0;
   int rho = 4;   // barycenter rows per lane of this set's sweeps
+  bool team = false;         // swept by teams of four waves a strip
   bool walk_pairs = false;   // path recovery one pair at a time, from checkpoints (CKPT sweep)
 };
 
@@ -65,6 +66,17 @@ struct Job {
   int64_t x_off, y_off;
   int32_t M, N, out;
 };
+
+// Strip row stride of the DTW sweeps (row_stride in wts_sweep.h).
+int64_t row_stride_host(int32_t N) { return (N + wts::kWave - 1 + 3) & ~3; }
+
+// Workspace of a score sweep with that many strip row elements (the layout of
+// WTS_OP_SCORE).
+size_t score_bytes(int64_t rows, int n) {
+  return align_up(2 * sizeof(int)) + align_up(sizeof(double) * (size_t)rows) +
+         align_up(sizeof(int) * (size_t)rows) + align_up(sizeof(double) * (size_t)n) +
+         align_up(sizeof(int) * (size_t)n);
+}
 
 void build_set(PairSet& ps, std::vector<Job> jobs, int rho, bool soft) {
   const int H = wts::kWave * rho;
@@ -100,7 +112,7 @@ void build_set(PairSet& ps, std::vector<Job> jobs, int rho, bool soft) {
     // checkpoints: every 16 steps (Soft-DTW), every 64 steps (DTW paths)
     state += (int64_t)d.S * (soft ? d.WT : (d.WT + 3) / 4) * (rho + 1) * wts::kWave;
     flags += d.S;
-    rows += (int64_t)d.S * ((jb.N + wts::kWave - 1 + 3) & ~3);   // strip row stride RS
+    rows += (int64_t)d.S * row_stride_host(jb.N);
     for (int s = 0; s < d.S; ++s) ps.items.push_back(make_int2((int)p, s));
     ps.pairs.push_back(d);
     ps.max_rows = std::max<int64_t>(ps.max_rows, jb.M);
@@ -144,23 +156,41 @@ constexpr int kMaxDevices = 64;
 std::mutex g_scratch_mu;
 void* g_scratch[kMaxDevices] = {};
 
+// Whether a set of `items` strips is swept by teams of four waves a strip
+// (wts_team.h) or by one wave a strip.  Teams win while the strips leave
+// compute units or SIMDs idle.  Score sweep / DBA iteration in us, team
+// against one wave, float64, d = 3: 8 x 4.4k (L = 4000) 559 / 736 against
+// 931 / 1136, 32 x 4.4k 761 / 903 against 957 / 1161; past five strips of two
+// rows a lane per compute unit the two are even (48 x 4.4k: 961 / 1128 against
+// 968 / 1168), and at seven the team loses (16 x 16k: 3941 / 4456 against
+// 3599 / 4321).  Teams of four rows a lane hold 64 KB of LDS (float64), two a
+// compute unit, and win up to that; in float32 they hold half of it.
+bool team_pays(int rho, int64_t items, int cus, bool fp32) {
+  if (rho == 2) return items <= 5 * (int64_t)cus;
+  return rho == 4 && items <= (fp32 ? 4 : 2) * (int64_t)cus;
+}
+
 // Rows per lane of the barycenter sweeps when the caller leaves it open.
-// With about one strip per SIMD, a strip that shares its SIMD slows its whole
-// chain, and the dispatcher does not spread workgroups perfectly once they
-// cover nearly every compute unit: such batches take 5 rows per lane when
-// that brings them under ~80 % of the SIMDs.  Small batches (one strip per
-// SIMD or less) keep 4.  Large float64 batches of two channels or more take 5
-// where the padding of the last strip allows it: a step costs about 2 d + 4
+// Batches of few strips take 2 and are swept by teams (in float32 above four
+// such strips a compute unit, teams of 4: 16 x 16k, d = 3, score / DBA 2526 /
+// 2973 us against 2746 / 3431).  With about one strip per SIMD, a strip that
+// shares its SIMD slows its whole chain, and the dispatcher does not spread
+// workgroups perfectly once they cover nearly every compute unit: such
+// batches take 5 rows per lane when that brings them under ~80 % of the
+// SIMDs, else 4.  Large float64 batches of two channels or more take 5 where
+// the padding of the last strip allows it: a step costs about 2 d + 4
 // instructions a row and 10 of its own, which 5 rows share (512 cycles of
 // 1k-20k samples, d = 6, L = 10,000: the checkpointed sweep 19.4 ms against
 // 20.7; the score sweep at d = 6 13 % and at d = 3 6 % faster).  At d = 1 the
 // two time alike, and in float32 the score sweep is 10 % slower at 5.
-int bary_rho(int64_t L, int n, int cus, int d, bool fp32) {
+int bary_rho(int64_t L, int n, int cus, int d, bool fp32, bool team) {
   auto strips = [&](int r) { return (L + 64 * r - 1) / (64 * r); };
   auto items = [&](int r) { return (int64_t)n * strips(r); };
   const int64_t simds = 4 * (int64_t)cus;
   const int64_t cap = simds * 13 / 16;
   const int64_t i4 = items(4);
+  if (team && fp32 && items(2) > simds && team_pays(4, i4, cus, fp32)) return 4;
+  if (team && team_pays(2, items(2), cus, fp32)) return 2;
   if (i4 > cap && i4 <= 2 * simds && items(5) <= cap) return 5;
   auto steps = [&](int r) { return strips(r) * (r * (2 * d + 4) + 10); };
   if (i4 > 2 * simds && d >= 2 && !fp32 && steps(5) < steps(4)) return 5;
@@ -249,7 +279,7 @@ Layout layout(const wts_plan* p, int op) {
     return l;
   }
   const bool paths = op == WTS_OP_ALIGN_PATHS || op == WTS_OP_DBA;
-  l.queue = take(2 * sizeof(int));   // [0] item counter, [1] status word
+  l.queue = take(2 * sizeof(int));   // item counter
   l.bnd_r = take(sizeof(double) * (size_t)ps.row_elems);
   l.bnd_aux = take(sizeof(int) * (size_t)(op == WTS_OP_MEDOID ? 0 : ps.row_elems));
   if (paths && ps.walk_pairs)
@@ -364,16 +394,15 @@ void timing_end(const wts_plan* p, int k, hipStream_t st) {
   if (k >= 0) (void)hipEventRecord(p->ev[2 * k + 1], st);
 }
 
-// Zero the queue, fill the strip rows with sentinels, then run the
+// Fill the strip rows with sentinels and zero the queue, then run the
 // persistent sweep.
 wts_status run_sweep(const wts_plan* p, const PairSet& ps, int mode, bool euc, bool x_is_cycle,
                      const void* x, const void* y, void* ws, const Layout& l, double* out_dist,
                      hipStream_t st) {
-  HIP_TRY(wts::launch_zero(at<int>(ws, l.queue), 2, st));
   HIP_TRY(wts::launch_fill_sentinels(at<double>(ws, l.bnd_r), ps.row_elems, at<int>(ws, l.bnd_aux),
                                      mode == wts::MODE_DIST_LEN || mode == wts::MODE_SUB ||
                                              mode == wts::MODE_PATHT
-                                         ? ps.row_elems : 0, st));
+                                         ? ps.row_elems : 0, at<int>(ws, l.queue), st));
   wts::FwdArgs a{};
   a.pairs = ps.d_pairs;
   a.items = ps.d_sweep_items;
@@ -395,8 +424,13 @@ wts_status run_sweep(const wts_plan* p, const PairSet& ps, int mode, bool euc, b
   const int tk = timing_begin(p, x_is_cycle ? WTS_OP_MEDOID
                                  : mode == wts::MODE_CKPT || mode == wts::MODE_PATHT ? WTS_OP_DBA
                                  : mode == wts::MODE_SUB ? WTS_OP_SUBDTW : WTS_OP_SCORE, st);
-  HIP_TRY(wts::launch_fwd(p->d, ps.rho, mode, euc, x_is_cycle, p->dtype,
-                          p->opts.decision == WTS_DECISION_FP32, a, default_grid(p, ps), st));
+  const bool fp32 = p->opts.decision == WTS_DECISION_FP32;
+  if (ps.team)   // at most the four workgroups a compute unit holds, and twice as many waiting
+    HIP_TRY(wts::launch_team(p->d, ps.rho, mode, euc, x_is_cycle, p->dtype, fp32, a,
+                             std::min(ps.n_items, 8 * p->cus), st));
+  else
+    HIP_TRY(wts::launch_fwd(p->d, ps.rho, mode, euc, x_is_cycle, p->dtype, fp32, a,
+                            default_grid(p, ps), st));
   timing_end(p, tk, st);
   return WTS_OK;
 }
@@ -516,8 +550,22 @@ wts_status wts_plan_create(wts_plan** out, int device, int32_t n, int32_t d, int
   if (L > 0) {
     for (int k = 0; k < n; ++k)
       jobs.push_back(Job{0, p->off[k], (int32_t)L, (int32_t)(p->off[k + 1] - p->off[k]), k});
-    build_set(p->bary, jobs, o.rho ? o.rho : bary_rho(L, n, p->cus, d, o.decision == WTS_DECISION_FP32),
-              false);
+    const bool fp32 = o.decision == WTS_DECISION_FP32;
+    const bool team = o.grid == 0;   // a grid asks for that many one-wave sweepers
+    int rho = o.rho ? o.rho : bary_rho(L, n, p->cus, d, fp32, team);
+    // more rows a lane leave fewer strip rows: a batch whose score workspace
+    // fits the scratch of wts_anomaly_score_noalloc only with those of the
+    // one-wave sweeps keeps them
+    auto scratch_fits = [&](int r) {
+      int64_t rows = 0;
+      for (const Job& jb : jobs)
+        rows += (int64_t)((jb.M + wts::kWave * r - 1) / (wts::kWave * r)) * row_stride_host(jb.N);
+      return score_bytes(rows, n) <= kScratchBytes;
+    };
+    const int alt = o.rho ? rho : bary_rho(L, n, p->cus, d, fp32, false);
+    if (alt != rho && !scratch_fits(rho) && scratch_fits(alt)) rho = alt;
+    build_set(p->bary, jobs, rho, false);
+    p->bary.team = team && team_pays(p->bary.rho, p->bary.n_items, p->cus, fp32);
     p->bary.walk_pairs = o.walk == WTS_WALK_PAIRS ||
                          (o.walk == WTS_WALK_AUTO && walk_pairs_pays(p->bary));
     build_set(p->soft, jobs, wts::kSoftRho, true);
@@ -543,6 +591,8 @@ wts_status wts_plan_create(wts_plan** out, int device, int32_t n, int32_t d, int
         else jobs.push_back(Job{p->off[b], p->off[a], (int32_t)lb, (int32_t)la, slot});
       }
     build_set(p->med, jobs, p->rho, false);
+    p->med.team = o.grid == 0 && team_pays(p->rho, p->med.n_items, p->cus,
+                                           o.decision == WTS_DECISION_FP32);
     if (!ab.empty()) {
       hipError_t e;
       if ((e = hipMalloc(&p->d_med_ab, sizeof(int2) * ab.size())) != hipSuccess) return cleanup_fail(e, "hipMalloc");

@@ -143,8 +143,10 @@ __global__ void zero_i32_kernel(int* p, int64_t n) {
     p[k] = 0;
 }
 
-// Sentinel fill of the strip boundary rows before a sweep.
-__global__ void fill_sent_kernel(unsigned long long* r, int64_t nr, int* x, int64_t nx) {
+// Sentinel fill of the strip boundary rows before a sweep, and its item
+// counter.
+__global__ void fill_sent_kernel(unsigned long long* r, int64_t nr, int* x, int64_t nx, int* queue) {
+  if (blockIdx.x == 0 && threadIdx.x == 0) *queue = 0;
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   for (int64_t k = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; k < nr; k += stride)
     r[k] = kSentR;
@@ -327,12 +329,12 @@ hipError_t launch_zero(int* p, int64_t n, hipStream_t st) {
   return hipGetLastError();
 }
 
-hipError_t launch_fill_sentinels(double* r, int64_t nr, int* x, int64_t nx, hipStream_t st) {
+hipError_t launch_fill_sentinels(double* r, int64_t nr, int* x, int64_t nx, int* queue,
+                                 hipStream_t st) {
   const int64_t n = nr > nx ? nr : nx;
-  if (n <= 0) return hipSuccess;
-  const int64_t blocks = (n + 255) / 256;
+  const int64_t blocks = n > 0 ? (n + 255) / 256 : 1;
   hipLaunchKernelGGL(fill_sent_kernel, dim3((unsigned)(blocks < 8192 ? blocks : 8192)), dim3(256), 0,
-                     st, reinterpret_cast<unsigned long long*>(r), nr, x, nx);
+                     st, reinterpret_cast<unsigned long long*>(r), nr, x, nx, queue);
   return hipGetLastError();
 }
 

@@ -35,6 +35,13 @@ hipError_t launch_fwd(int d, int rho, int mode, bool euc, bool x_is_cycle, int y
                       const FwdArgs& a, int grid, hipStream_t st);
 hipError_t launch_fwd32(int d, int rho, int mode, bool euc, bool x_is_cycle, int ydtype,
                         const FwdArgs& a, int grid, hipStream_t st);
+// The team sweeps (four waves a strip, rho 2 or 4); groups: workgroups.
+hipError_t launch_team(int d, int rho, int mode, bool euc, bool x_is_cycle, int ydtype, bool fp32,
+                       const FwdArgs& a, int groups, hipStream_t st);
+hipError_t launch_team4(int d, int mode, bool euc, bool x_is_cycle, int ydtype, const FwdArgs& a,
+                        int groups, hipStream_t st);
+hipError_t launch_team32(int d, int rho, int mode, bool euc, bool x_is_cycle, int ydtype,
+                         const FwdArgs& a, int groups, hipStream_t st);
 // Path recovery after a PATHT sweep: the strip chain (segments from the
 // entry tags), then walks of all strips at once (row runs).
 hipError_t launch_walk(int rho, const WalkArgs& a, int n_items, hipStream_t st);
@@ -54,7 +61,8 @@ hipError_t launch_run_fold(int d, int ydtype, const int2* runs, const int64_t* o
 hipError_t launch_emit(const int2* runs, const int64_t* path_base, int n, int64_t L,
                        int32_t* paths, int64_t* path_len, const int* skip, hipStream_t st);
 hipError_t launch_zero(int* p, int64_t n, hipStream_t st);
-hipError_t launch_fill_sentinels(double* r, int64_t nr, int* x, int64_t nx, hipStream_t st);
+hipError_t launch_fill_sentinels(double* r, int64_t nr, int* x, int64_t nx, int* queue,
+                                 hipStream_t st);
 hipError_t launch_score(const double* dist, const int* len, int n, double* score,
                         int64_t* path_len, hipStream_t st);
 hipError_t launch_sub_out(const int* start, const int* end, int n, int64_t* a_star,
