@@ -58,6 +58,7 @@ struct PairSet {
   int64_t code_words = 0, bnd_elems = 0, aux_strip_elems = 0, state_elems = 0, row_elems = 0;
   int64_t max_rows = 0;
   int rho = 4;   // barycenter rows per lane of this set's sweeps
+  int waves = 1;             // one-wave sweeps: waves per SIMD
   bool team = false;         // swept by teams of four waves a strip
   bool walk_pairs = false;   // path recovery one pair at a time, from checkpoints (CKPT sweep)
 };
@@ -173,28 +174,52 @@ bool team_pays(int rho, int64_t items, int cus, bool fp32) {
 // Rows per lane of the barycenter sweeps when the caller leaves it open.
 // Batches of few strips take 2 and are swept by teams (in float32 above four
 // such strips a compute unit, teams of 4: 16 x 16k, d = 3, score / DBA 2526 /
-// 2973 us against 2746 / 3431).  With about one strip per SIMD, a strip that
-// shares its SIMD slows its whole chain, and the dispatcher does not spread
-// workgroups perfectly once they cover nearly every compute unit: such
-// batches take 5 rows per lane when that brings them under ~80 % of the
-// SIMDs, else 4.  Large float64 batches of two channels or more take 5 where
-// the padding of the last strip allows it: a step costs about 2 d + 4
-// instructions a row and 10 of its own, which 5 rows share (512 cycles of
-// 1k-20k samples, d = 6, L = 10,000: the checkpointed sweep 19.4 ms against
-// 20.7; the score sweep at d = 6 13 % and at d = 3 6 % faster).  At d = 1 the
-// two time alike, and in float32 the score sweep is 10 % slower at 5.
+// 2973 us against 2746 / 3431).  Others take 4, with one wave to a SIMD and
+// one workgroup to a compute unit up to 1024 strips.  Float64 batches of two
+// channels or more and of more than four strips a SIMD take 5 where the
+// padding of the last strip allows it: a step costs about 2 d + 4
+// instructions a row and 10 of its own, which 5 rows share (40 cycles of
+// 40k-50k samples, d = 6, score / checkpointed sweep: 74.3 / 61.2 ms against
+// 77.7 / 64.8; 25 of 30k: 22.9 / 19.2 against 20.6 / 18.2).  In float32 the
+// score sweep is no faster at 5.
 int bary_rho(int64_t L, int n, int cus, int d, bool fp32, bool team) {
   auto strips = [&](int r) { return (L + 64 * r - 1) / (64 * r); };
   auto items = [&](int r) { return (int64_t)n * strips(r); };
   const int64_t simds = 4 * (int64_t)cus;
-  const int64_t cap = simds * 13 / 16;
-  const int64_t i4 = items(4);
-  if (team && fp32 && items(2) > simds && team_pays(4, i4, cus, fp32)) return 4;
+  if (team && fp32 && items(2) > simds && team_pays(4, items(4), cus, fp32)) return 4;
   if (team && team_pays(2, items(2), cus, fp32)) return 2;
-  if (i4 > cap && i4 <= 2 * simds && items(5) <= cap) return 5;
   auto steps = [&](int r) { return strips(r) * (r * (2 * d + 4) + 10); };
-  if (i4 > 2 * simds && d >= 2 && !fp32 && steps(5) < steps(4)) return 5;
+  if (items(4) > 4 * simds && d >= 2 && !fp32 && steps(5) < steps(4)) return 5;
   return 4;
+}
+
+// Waves per SIMD of the one-wave sweeps.  A second wave on a SIMD raises its
+// throughput (a step of both takes 1.67 times a step of one in float64, 1.3
+// in float32) and slows the chain of every pair's strips by as much, and the
+// deeper the strips of a pair are resident, the longer they wait for each
+// other at the start (about 300 steps a strip).  In steps of one wave: the
+// longest pair's chain, or all strips over the SIMDs.  Measured, score sweep
+// of d = 3 at 1 / 2 / 3 waves: 20 cycles of 2.5k-40k samples (L = 20,000) 7.3
+// / 10.4 / 10.2 ms, 50 of 20k 13.0 / 14.0 / 14.0, 512 of 1k-20k (L = 10,000)
+// 20.7 / 17.2 / 18.3.  Three waves gain where the instruction mix is light:
+// value sweeps of few channels (medoid of 64 x 5k, d = 3: 16.6 / 16.2 ms at 2 /
+// 3) and float32 (512 cycles, d = 6: 17.7 / 17.1).
+int sweep_waves(const PairSet& ps, int cus, int d, bool fp32, bool values) {
+  const double simds = 4.0 * cus;
+  double work = 0.0, chain = 0.0, smax = 0.0;
+  for (const PairDesc& q : ps.pairs) {
+    const double steps = 16.0 * q.WT;
+    work += steps * q.S;
+    chain = std::max(chain, steps + 120.0 * q.S);
+    smax = std::max(smax, (double)q.S);
+  }
+  if (ps.n_items <= simds) return 1;
+  work /= simds;
+  auto depth = [&](int w) { return std::min(smax, w * simds / std::max(1, ps.n_pairs)); };
+  const double one = std::max(chain, work + 120.0 * depth(1));
+  const double two = (fp32 ? 1.3 : 1.67) * std::max(chain, work / 2 + 300.0 * depth(2));
+  if (one <= two) return 1;
+  return (values && d <= 4) || (fp32 && ps.n_items > 6 * simds) ? 3 : 2;
 }
 
 }  // namespace
@@ -305,30 +330,42 @@ Layout layout(const wts_plan* p, int op) {
 template <typename T>
 T* at(void* ws, size_t off) { return reinterpret_cast<T*>(static_cast<char*>(ws) + off); }
 
-// Path recovery.  Codes and entry tags for every cell (PATHT) cost the sweep
-// a fifth to a third of its time and let all strips be walked at once, in
-// about 0.1 ms.  From checkpoints (CKPT) the sweep is the value sweep, and
-// each pair's strips are swept again along its path and walked in turn, about
-// 35 us a strip.  Measured per DBA iteration, codes against checkpoints: 512
-// cycles of 1k-20k samples (L = 10,000, 3.2e10 cells) 25.4 / 22.8 ms, 40
-// cycles of 40k-50k samples in float32 decisions 51.9 / 40.0 ms, 64 cycles of
-// 4k-6k samples 1.46 / 1.42 ms, 24 cycles of 1.5k-2.5k samples 0.79 / 0.85 ms.
-// Checkpoints pay when the codes and tags, about 1.5e-13 s a cell, cost more
-// than the longest pair's strips.
-bool walk_pairs_pays(const PairSet& ps) {
-  double cells = 0.0;
+// Path recovery.  Codes and entry tags for every cell (PATHT) cost the
+// one-wave sweep about 28 instructions a step of 4 rows (62 ns with one wave
+// to a SIMD, 36 ns with more) and let all strips be walked at once, in about
+// 0.1 ms.  From checkpoints (CKPT) the sweep is the value sweep, and each
+// pair's strips are swept again along its path and walked in turn, 23 us and
+// 2.4 us a channel a strip (above 256 pairs they share the compute units).
+// Measured per DBA iteration, codes / checkpoints: 512 cycles of 1k-20k
+// samples (L = 10,000, d = 6) 25.3 / 22.8 ms, 25 of 30k (d = 3) 18.1 / 15.5,
+// 25 of 30k (d = 8) 27.0 / 27.2, 64 of 4k (d = 3) 1.27 / 1.22.  A team's sweep
+// costs less a strip than its walk: codes.
+bool walk_pairs_pays(const PairSet& ps, int cus, int d) {
+  if (ps.team) return false;
+  double work = 0.0, chain = 0.0;
   int smax = 0;
-  for (const PairDesc& d : ps.pairs) {
-    cells += (double)d.M * (double)d.N;
-    smax = std::max(smax, d.S);
+  for (const PairDesc& q : ps.pairs) {
+    const double steps = 16.0 * q.WT;
+    work += steps * q.S;
+    chain = std::max(chain, steps + 120.0 * q.S);
+    smax = std::max(smax, q.S);
   }
-  return cells * 1.5e-13 > smax * 35e-6;
+  const double steps = std::max(chain, work / (4.0 * cus));
+  return steps * (ps.waves == 1 ? 62e-9 : 36e-9) * ps.rho / 4 >
+         smax * (23e-6 + 2.4e-6 * d) * std::max(1.0, ps.n_pairs / 256.0);
 }
 
-int default_grid(const wts_plan* p, const PairSet& ps) {
-  // 24 one-wave workgroups per CU: enough resident waves for the value sweep
-  // (6 per SIMD); the path sweep's register budget caps it lower by itself.
+int default_grid(const wts_plan* p, const PairSet& ps) {   // Soft-DTW sweeps
+  // 24 one-wave workgroups per CU; the sweeps' registers cap the resident
+  // waves lower by themselves.
   const int g = p->opts.grid > 0 ? p->opts.grid : p->cus * 24;
+  return std::max(1, std::min(g, ps.n_items));
+}
+
+// Waves of a one-wave DTW sweep: the caller's, or ps.waves to a SIMD (four to
+// a workgroup, ps.waves workgroups to a compute unit).
+int dtw_grid(const wts_plan* p, const PairSet& ps) {
+  const int g = p->opts.grid > 0 ? p->opts.grid : 4 * p->cus * ps.waves;
   return std::max(1, std::min(g, ps.n_items));
 }
 
@@ -420,6 +457,7 @@ wts_status run_sweep(const wts_plan* p, const PairSet& ps, int mode, bool euc, b
   a.out_aux = at<int>(ws, l.out_aux);
   a.out_end = mode == wts::MODE_SUB ? at<int>(ws, l.out_end) : nullptr;
   a.cost_kind = euc ? 1 : 0;
+  a.per_cu = p->opts.grid > 0 ? 0 : ps.waves;
   a.relaxed_wait = ps.n_items > 16 * p->cus ? 1 : 0;   // > 4 items per SIMD
   const int tk = timing_begin(p, x_is_cycle ? WTS_OP_MEDOID
                                  : mode == wts::MODE_CKPT || mode == wts::MODE_PATHT ? WTS_OP_DBA
@@ -430,7 +468,7 @@ wts_status run_sweep(const wts_plan* p, const PairSet& ps, int mode, bool euc, b
                              std::min(ps.n_items, 8 * p->cus), st));
   else
     HIP_TRY(wts::launch_fwd(p->d, ps.rho, mode, euc, x_is_cycle, p->dtype, fp32, a,
-                            default_grid(p, ps), st));
+                            dtw_grid(p, ps), st));
   timing_end(p, tk, st);
   return WTS_OK;
 }
@@ -566,8 +604,9 @@ wts_status wts_plan_create(wts_plan** out, int device, int32_t n, int32_t d, int
     if (alt != rho && !scratch_fits(rho) && scratch_fits(alt)) rho = alt;
     build_set(p->bary, jobs, rho, false);
     p->bary.team = team && team_pays(p->bary.rho, p->bary.n_items, p->cus, fp32);
+    p->bary.waves = sweep_waves(p->bary, p->cus, d, fp32, false);
     p->bary.walk_pairs = o.walk == WTS_WALK_PAIRS ||
-                         (o.walk == WTS_WALK_AUTO && walk_pairs_pays(p->bary));
+                         (o.walk == WTS_WALK_AUTO && walk_pairs_pays(p->bary, p->cus, d));
     build_set(p->soft, jobs, wts::kSoftRho, true);
     std::vector<Job> tjobs;
     for (int k = 0; k < n; ++k)
@@ -591,8 +630,9 @@ wts_status wts_plan_create(wts_plan** out, int device, int32_t n, int32_t d, int
         else jobs.push_back(Job{p->off[b], p->off[a], (int32_t)lb, (int32_t)la, slot});
       }
     build_set(p->med, jobs, p->rho, false);
-    p->med.team = o.grid == 0 && team_pays(p->rho, p->med.n_items, p->cus,
-                                           o.decision == WTS_DECISION_FP32);
+    const bool fp32 = o.decision == WTS_DECISION_FP32;
+    p->med.team = o.grid == 0 && team_pays(p->rho, p->med.n_items, p->cus, fp32);
+    p->med.waves = sweep_waves(p->med, p->cus, d, fp32, true);
     if (!ab.empty()) {
       hipError_t e;
       if ((e = hipMalloc(&p->d_med_ab, sizeof(int2) * ab.size())) != hipSuccess) return cleanup_fail(e, "hipMalloc");

@@ -106,8 +106,7 @@ struct FwdArgs {
   int cost_kind;         // 0 squared, 1 Euclidean (sqrt)
   int relaxed_wait;      // 1: far more items than resident wavefronts; wait with long sleeps
   const int* skip;       // non-zero flag: the call's inputs failed validation, do nothing (or null)
-  int zero_skip;         // backward: 1 = tiles whose e is exactly zero are not swept
-  unsigned long long* tiles;   // backward: += tiles swept, tiles of the strips' ranges (or null)
+  int per_cu;            // one-wave sweeps, host only: workgroups a compute unit may hold (0: any)
 };
 
 struct SoftArgs {

@@ -470,10 +470,17 @@ inline unsigned sweep_groups(int grid) {
     default: return hipErrorInvalidValue; \
   }
 
+// a.per_cu > 0: that many workgroups to a compute unit, enforced by the LDS
+// they ask for (a dispatcher that put two of them on one unit and none on
+// another would halve the pace of the strips that share it).
+constexpr int kCuLds = 160 * 1024;
 template <typename TX, typename TY, typename TC, int D, int RHO, int MODE, bool EUC>
 hipError_t launch_one(const FwdArgs& a, int grid, hipStream_t st) {
+  constexpr int fixed = kSweepWaves * (int)(sizeof(TC) * (D * (kRing + 16) + 16 + 32 + kWave) +
+                                            sizeof(int) * (16 + 32 + kWave + 1));
+  const int want = a.per_cu > 0 ? kCuLds / (a.per_cu + 1) + 1024 : 0;
   hipLaunchKernelGGL((dtw_fwd_kernel<TX, TY, TC, D, RHO, MODE, EUC>), dim3(sweep_groups(grid)),
-                     dim3(kWave * kSweepWaves), 0, st, a);
+                     dim3(kWave * kSweepWaves), want > fixed ? want - fixed : 0, st, a);
   return hipGetLastError();
 }
 
