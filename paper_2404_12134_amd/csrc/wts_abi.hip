@@ -277,7 +277,7 @@ Layout layout(const wts_plan* p, int op) {
   if (op == WTS_OP_SOFT_GRAD_C) {   // the transposed forward and backward in one buffer
     const int64_t rows = p->off[p->n];
     l.queue = take(2 * sizeof(int));
-    l.progress = take(sizeof(int) * (size_t)ps.n_flags);
+    l.progress = take(3 * sizeof(int) * (size_t)ps.n_flags);
     l.rows = take(sizeof(double) * (size_t)ps.aux_strip_elems);
     l.states = take(sizeof(double) * (size_t)ps.state_elems);
     l.push_up = take(sizeof(float) * (size_t)ps.bnd_elems);
@@ -290,7 +290,7 @@ Layout layout(const wts_plan* p, int op) {
   }
   if (op == WTS_OP_SOFT_FWD || op == WTS_OP_SOFT_BWD) {
     l.queue = take(2 * sizeof(int));
-    l.progress = take(sizeof(int) * (size_t)ps.n_flags);
+    l.progress = take((op == WTS_OP_SOFT_FWD ? 1 : 3) * sizeof(int) * (size_t)ps.n_flags);
     if (op == WTS_OP_SOFT_FWD) {
       l.rows = take(sizeof(double) * (size_t)ps.aux_strip_elems);
       l.states = take(sizeof(double) * (size_t)ps.state_elems);
@@ -359,6 +359,13 @@ int default_grid(const wts_plan* p, const PairSet& ps) {   // Soft-DTW sweeps
   // 24 one-wave workgroups per CU; the sweeps' registers cap the resident
   // waves lower by themselves.
   const int g = p->opts.grid > 0 ? p->opts.grid : p->cus * 24;
+  return std::max(1, std::min(g, ps.n_items));
+}
+
+// Workgroups of the Soft-DTW backward: one to a compute unit (its LDS), and one
+// waiting.
+int bwd_grid(const wts_plan* p, const PairSet& ps) {
+  const int g = p->opts.grid > 0 ? p->opts.grid : 2 * p->cus;
   return std::max(1, std::min(g, ps.n_items));
 }
 
@@ -958,8 +965,9 @@ wts_status wts_softdtw_backward(const wts_plan* p, const double* bary, const voi
   const PairSet& ps = p->soft;
   void* ck = const_cast<void*>(ckpt);
   HIP_TRY(wts::launch_zero(at<int>(ws, l.queue), 2, st));
-  HIP_TRY(wts::launch_zero(at<int>(ws, l.progress), ps.n_flags, st));
+  HIP_TRY(wts::launch_zero(at<int>(ws, l.progress), 3 * (int64_t)ps.n_flags, st));
   wts::SoftArgs a{};
+  a.n_flags = ps.n_flags;
   a.pairs = ps.d_pairs;
   a.items = ps.d_items_rev;
   a.n_items = ps.n_items;
@@ -982,7 +990,7 @@ wts_status wts_softdtw_backward(const wts_plan* p, const double* bary, const voi
   a.zero_skip = p->opts.dense_e ? 0 : 1;
   a.tiles = p->d_tiles;
   const int tk = timing_begin(p, WTS_OP_SOFT_BWD, st);
-  HIP_TRY(wts::launch_soft(p->d, p->dtype, true, a, default_grid(p, ps), st));
+  HIP_TRY(wts::launch_soft(p->d, p->dtype, true, a, bwd_grid(p, ps), st));
   timing_end(p, tk, st);
   HIP_TRY(wts::launch_soft_reduce(a.gsum, a.hsum, grad_value, p->n, p->L, p->d, grad_bary,
                                   row_mass, accumulate, st));
@@ -1030,11 +1038,12 @@ wts_status wts_softdtw_grad_cycles(const wts_plan* p, const double* bary, const 
   a.items = ps.d_sweep_items;
   HIP_TRY(wts::launch_soft(p->d, WTS_F64, false, a, default_grid(p, ps), st));
   HIP_TRY(wts::launch_zero(a.queue, 2, st));
-  HIP_TRY(wts::launch_zero(a.progress, ps.n_flags, st));
+  HIP_TRY(wts::launch_zero(a.progress, 3 * (int64_t)ps.n_flags, st));
   a.items = ps.d_items_rev;
+  a.n_flags = ps.n_flags;
   a.zero_skip = p->opts.dense_e ? 0 : 1;
   a.tiles = p->d_tiles;
-  HIP_TRY(wts::launch_soft(p->d, WTS_F64, true, a, default_grid(p, ps), st));
+  HIP_TRY(wts::launch_soft(p->d, WTS_F64, true, a, bwd_grid(p, ps), st));
   HIP_TRY(wts::launch_soft_rows_scale(a.gsum, p->d_off, p->n, p->off[p->n], p->d, grad_value,
                                       grad_cycles, st));
   return WTS_OK;

@@ -115,7 +115,8 @@ struct SoftArgs {
   int n_items;
   int* queue;
   int* status;
-  int* progress;
+  int* progress;         // per strip: columns published; the backward: three words a strip (BwdWords)
+  int n_flags;           // strips of the pair set
   const double* x;       // row series: the barycenter [L][d], or packed float64 cycles (x_off)
   const void* y;         // column series: cycle values, or the barycenter
   double* rows;          // bottom row of every strip, scaled units (S * N per pair)
@@ -243,6 +244,16 @@ __device__ __forceinline__ void mem_wait_all_but_1() {
 __device__ __forceinline__ void mem_wait_all_but_2() {
   __atomic_signal_fence(__ATOMIC_SEQ_CST);
   __builtin_amdgcn_s_waitcnt(0x0F72);
+  __atomic_signal_fence(__ATOMIC_SEQ_CST);
+}
+
+// A workgroup barrier that orders LDS accesses only (lgkmcnt 0): the waves'
+// global loads and stores stay in flight across it, where __syncthreads would
+// wait for a trip to memory in every phase.
+__device__ __forceinline__ void team_barrier() {
+  __atomic_signal_fence(__ATOMIC_SEQ_CST);
+  __builtin_amdgcn_s_waitcnt(0xC07F);
+  __builtin_amdgcn_s_barrier();
   __atomic_signal_fence(__ATOMIC_SEQ_CST);
 }
 

@@ -25,16 +25,6 @@ namespace {
 constexpr int kTeamGroup = 16;   // steps per phase
 constexpr int kTeamWaves = 4;
 
-// A workgroup barrier that orders LDS accesses only (lgkmcnt 0): the waves'
-// global loads and stores stay in flight across it, where __syncthreads would
-// wait for a trip to memory in every phase.
-__device__ __forceinline__ void team_barrier() {
-  __atomic_signal_fence(__ATOMIC_SEQ_CST);
-  __builtin_amdgcn_s_waitcnt(0xC07F);
-  __builtin_amdgcn_s_barrier();
-  __atomic_signal_fence(__ATOMIC_SEQ_CST);
-}
-
 template <typename TX, typename TY, typename TC, int D, int RHO, int MODE, bool EUC>
 __global__ __launch_bounds__(kWave * kTeamWaves) void dtw_team_kernel(FwdArgs a) {
   constexpr int H = kWave * RHO;
