@@ -171,6 +171,16 @@ bool team_pays(int rho, int64_t items, int cus, bool fp32) {
   return rho == 4 && items <= (fp32 ? 4 : 2) * (int64_t)cus;
 }
 
+// The Soft-DTW forward: teams of four waves a strip (wts_soft_team.hip) or one
+// wave a strip.  A team takes half the time a step and follows the strip above
+// at half the distance; one wave a strip has fewer instructions a cell once
+// the SIMDs are full.  Team against one wave, ms: 16 x 2k (256 strips, d = 3)
+// 0.44 / 0.98, 5 x 18k 4.3 / 9.4, 25 x 18k (3600 strips) 10.0 / 14.9, 100 x 8k
+// (6300 strips) 6.8 / 8.3 and at d = 6 8.7 / 9.1, 400 x 2k (6400) 1.77 / 2.01
+// and at d = 6 2.27 / 2.23, 200 x 8k (12,600) 12.4 / 12.9 and at d = 6 16.3 /
+// 14.6.
+bool soft_team_pays(int64_t items, int cus) { return items <= 24 * (int64_t)cus; }
+
 // Rows per lane of the barycenter sweeps when the caller leaves it open.
 // Batches of few strips take 2 and are swept by teams (in float32 above four
 // such strips a compute unit, teams of 4: 16 x 16k, d = 3, score / DBA 2526 /
@@ -181,16 +191,24 @@ bool team_pays(int rho, int64_t items, int cus, bool fp32) {
 // instructions a row and 10 of its own, which 5 rows share (40 cycles of
 // 40k-50k samples, d = 6, score / checkpointed sweep: 74.3 / 61.2 ms against
 // 77.7 / 64.8; 25 of 30k: 22.9 / 19.2 against 20.6 / 18.2).  In float32 the
-// score sweep is no faster at 5.
-int bary_rho(int64_t L, int n, int cus, int d, bool fp32, bool team) {
+// score sweep is no faster at 5.  Up to four strips a SIMD the longest pair's
+// chain (120 steps a strip) or the rounds of strips on the SIMDs decide, at
+// about 2 d + 8 instructions a row and 20 a step: 5 rows a lane win where they
+// save a strip or a round (500 cycles of 300, L = 300, one strip instead of
+// two: 72 against 85 us).
+int bary_rho(int64_t L, int n, int64_t nmax, int cus, int d, bool fp32, bool team) {
   auto strips = [&](int r) { return (L + 64 * r - 1) / (64 * r); };
   auto items = [&](int r) { return (int64_t)n * strips(r); };
   const int64_t simds = 4 * (int64_t)cus;
   if (team && fp32 && items(2) > simds && team_pays(4, items(4), cus, fp32)) return 4;
   if (team && team_pays(2, items(2), cus, fp32)) return 2;
   auto steps = [&](int r) { return strips(r) * (r * (2 * d + 4) + 10); };
-  if (items(4) > 4 * simds && d >= 2 && !fp32 && steps(5) < steps(4)) return 5;
-  return 4;
+  if (items(4) > 4 * simds) return d >= 2 && !fp32 && steps(5) < steps(4) ? 5 : 4;
+  auto chain = [&](int r) {
+    const int64_t rounds = (items(r) + simds - 1) / simds, one = nmax + wts::kWave;
+    return std::max(one + 120 * strips(r), rounds * one) * (r * (2 * d + 8) + 20);
+  };
+  return chain(5) * 100 < chain(4) * 97 ? 5 : 4;
 }
 
 // Waves per SIMD of the one-wave sweeps.  A second wave on a SIMD raises its
@@ -438,6 +456,25 @@ void timing_end(const wts_plan* p, int k, hipStream_t st) {
   if (k >= 0) (void)hipEventRecord(p->ev[2 * k + 1], st);
 }
 
+// The Soft-DTW forward of a pair set: by teams (strip rows filled with
+// sentinels) or by one wave a strip (progress counters zeroed).
+wts_status run_soft_fwd(const wts_plan* p, const PairSet& ps, int op, int dtype,
+                        const wts::SoftArgs& a, hipStream_t st) {
+  if (ps.team) {
+    HIP_TRY(wts::launch_fill_sentinels(a.rows, ps.aux_strip_elems, nullptr, 0, a.queue, st));
+  } else {
+    HIP_TRY(wts::launch_zero(a.queue, 2, st));
+    HIP_TRY(wts::launch_zero(a.progress, ps.n_flags, st));
+  }
+  const int tk = op == WTS_OP_SOFT_FWD ? timing_begin(p, op, st) : -1;
+  if (ps.team)
+    HIP_TRY(wts::launch_soft_team(p->d, dtype, a, std::min(ps.n_items, 4 * p->cus), st));
+  else
+    HIP_TRY(wts::launch_soft_fwd(p->d, dtype, a, default_grid(p, ps), st));
+  timing_end(p, tk, st);
+  return WTS_OK;
+}
+
 // Fill the strip rows with sentinels and zero the queue, then run the
 // persistent sweep.
 wts_status run_sweep(const wts_plan* p, const PairSet& ps, int mode, bool euc, bool x_is_cycle,
@@ -597,7 +634,7 @@ wts_status wts_plan_create(wts_plan** out, int device, int32_t n, int32_t d, int
       jobs.push_back(Job{0, p->off[k], (int32_t)L, (int32_t)(p->off[k + 1] - p->off[k]), k});
     const bool fp32 = o.decision == WTS_DECISION_FP32;
     const bool team = o.grid == 0;   // a grid asks for that many one-wave sweepers
-    int rho = o.rho ? o.rho : bary_rho(L, n, p->cus, d, fp32, team);
+    int rho = o.rho ? o.rho : bary_rho(L, n, p->nmax, p->cus, d, fp32, team);
     // more rows a lane leave fewer strip rows: a batch whose score workspace
     // fits the scratch of wts_anomaly_score_noalloc only with those of the
     // one-wave sweeps keeps them
@@ -607,7 +644,7 @@ wts_status wts_plan_create(wts_plan** out, int device, int32_t n, int32_t d, int
         rows += (int64_t)((jb.M + wts::kWave * r - 1) / (wts::kWave * r)) * row_stride_host(jb.N);
       return score_bytes(rows, n) <= kScratchBytes;
     };
-    const int alt = o.rho ? rho : bary_rho(L, n, p->cus, d, fp32, false);
+    const int alt = o.rho ? rho : bary_rho(L, n, p->nmax, p->cus, d, fp32, false);
     if (alt != rho && !scratch_fits(rho) && scratch_fits(alt)) rho = alt;
     build_set(p->bary, jobs, rho, false);
     p->bary.team = team && team_pays(p->bary.rho, p->bary.n_items, p->cus, fp32);
@@ -619,6 +656,8 @@ wts_status wts_plan_create(wts_plan** out, int device, int32_t n, int32_t d, int
     for (int k = 0; k < n; ++k)
       tjobs.push_back(Job{p->off[k], 0, (int32_t)(p->off[k + 1] - p->off[k]), (int32_t)L, k});
     build_set(p->softT, tjobs, wts::kSoftRho, true);
+    p->soft.team = team && soft_team_pays(p->soft.n_items, p->cus);
+    p->softT.team = team && soft_team_pays(p->softT.n_items, p->cus);
     std::vector<int64_t> base(n);
     for (int k = 0; k < n; ++k) base[k] = (int64_t)k * (L - 1) + p->off[k];
     hipError_t e;
@@ -919,8 +958,6 @@ wts_status wts_softdtw_forward(const wts_plan* p, const double* bary, const void
     return rc;
   const Layout l = layout(p, WTS_OP_SOFT_FWD);
   const PairSet& ps = p->soft;
-  HIP_TRY(wts::launch_zero(at<int>(ckpt, l.queue), 2, st));
-  HIP_TRY(wts::launch_zero(at<int>(ckpt, l.progress), ps.n_flags, st));
   wts::SoftArgs a{};
   a.pairs = ps.d_pairs;
   a.items = ps.d_sweep_items;
@@ -938,10 +975,7 @@ wts_status wts_softdtw_forward(const wts_plan* p, const double* bary, const void
   a.band = p->opts.band;
   a.value = value;
   a.L = p->L;
-  const int tk = timing_begin(p, WTS_OP_SOFT_FWD, st);
-  HIP_TRY(wts::launch_soft(p->d, p->dtype, false, a, default_grid(p, ps), st));
-  timing_end(p, tk, st);
-  return WTS_OK;
+  return run_soft_fwd(p, ps, WTS_OP_SOFT_FWD, p->dtype, a, st);
 }
 
 wts_status wts_softdtw_backward(const wts_plan* p, const double* bary, const void* cycles,
@@ -990,7 +1024,7 @@ wts_status wts_softdtw_backward(const wts_plan* p, const double* bary, const voi
   a.zero_skip = p->opts.dense_e ? 0 : 1;
   a.tiles = p->d_tiles;
   const int tk = timing_begin(p, WTS_OP_SOFT_BWD, st);
-  HIP_TRY(wts::launch_soft(p->d, p->dtype, true, a, bwd_grid(p, ps), st));
+  HIP_TRY(wts::launch_soft_bwd(p->d, p->dtype, a, bwd_grid(p, ps), st));
   timing_end(p, tk, st);
   HIP_TRY(wts::launch_soft_reduce(a.gsum, a.hsum, grad_value, p->n, p->L, p->d, grad_bary,
                                   row_mass, accumulate, st));
@@ -1033,17 +1067,15 @@ wts_status wts_softdtw_grad_cycles(const wts_plan* p, const double* bary, const 
   a.hsum = at<double>(ws, l.hsum);
   a.L = p->L;
   a.rows_packed = 1;
-  HIP_TRY(wts::launch_zero(a.queue, 2, st));
-  HIP_TRY(wts::launch_zero(a.progress, ps.n_flags, st));
   a.items = ps.d_sweep_items;
-  HIP_TRY(wts::launch_soft(p->d, WTS_F64, false, a, default_grid(p, ps), st));
+  if ((rc = run_soft_fwd(p, ps, WTS_OP_SOFT_GRAD_C, WTS_F64, a, st)) != WTS_OK) return rc;
   HIP_TRY(wts::launch_zero(a.queue, 2, st));
   HIP_TRY(wts::launch_zero(a.progress, 3 * (int64_t)ps.n_flags, st));
   a.items = ps.d_items_rev;
   a.n_flags = ps.n_flags;
   a.zero_skip = p->opts.dense_e ? 0 : 1;
   a.tiles = p->d_tiles;
-  HIP_TRY(wts::launch_soft(p->d, WTS_F64, true, a, bwd_grid(p, ps), st));
+  HIP_TRY(wts::launch_soft_bwd(p->d, WTS_F64, a, bwd_grid(p, ps), st));
   HIP_TRY(wts::launch_soft_rows_scale(a.gsum, p->d_off, p->n, p->off[p->n], p->d, grad_value,
                                       grad_cycles, st));
   return WTS_OK;

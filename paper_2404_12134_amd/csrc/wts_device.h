@@ -138,6 +138,13 @@ struct SoftArgs {
 
 __device__ __forceinline__ double inf_d() { return __builtin_huge_val(); }
 
+// Sentinel of a strip row's values that are not written yet.
+// The sentinel is a NaN that no arithmetic makes, read as one float64 or as
+// two float32 words (the float32-decision sweeps keep float32 rows in the
+// same buffer); both halves are the float32 sentinel.
+constexpr unsigned long long kSentR = 0xFFF4DEADFFF4DEADull;
+constexpr unsigned kSentR32 = 0xFFF4DEADu;
+
 // Status bits of a plan's device status word (sticky until wts_plan_status
 // reads and clears it).
 constexpr int kStatusSpinTimeout = 1;   // a strip gave up waiting for its predecessor

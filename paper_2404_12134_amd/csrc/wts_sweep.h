@@ -49,11 +49,6 @@ constexpr int kRing = 128;          // Y columns kept in LDS (>= kChunk + 63, po
 // after the whole block was filled with sentinels.  The strip below polls the values
 // themselves: a value is ready once it is no longer the sentinel, so no
 // progress counter, fence or store drain is needed between strips.
-// The sentinel is a NaN that no arithmetic makes, read as one float64 or as
-// two float32 words (the float32-decision sweeps keep float32 rows in the
-// same buffer); both halves are the float32 sentinel.
-constexpr unsigned long long kSentR = 0xFFF4DEADFFF4DEADull;
-constexpr unsigned kSentR32 = 0xFFF4DEADu;
 constexpr int kSentX = INT_MIN;
 __device__ __forceinline__ int row_stride(int N) { return (N + 63 + 3) & ~3; }
 
