@@ -13,15 +13,16 @@ namespace {
 //                below and above;
 //   waves 1..4   the replay: each takes every fourth tile, four steps of it a
 //                phase, and leaves the soft-min weights in LDS;
-//   wave 5       the row sums of the tile pushed in the phase before, and the Y
-//                columns of the tile whose replay begins in the next phase.
+//   waves 5, 6   the row sums (a row of the lane each) of the tile pushed in the
+//                phase before; wave 5 also brings in the Y columns of the tile
+//                whose replay begins in the next phase.
 // What bounds it is the chain of a pair's strips: a strip's e reaches the
 // strip above only after 63 + 128 steps (the lanes' skew and the columns a path
 // moves in 128 rows), so a tile's time counts twelve times a strip.  One wave
 // that replayed, pushed and summed its tiles in turn took 5.5 to 7 us a tile;
 // a phase takes about a fifth of it.
 constexpr int kBwdReplay = 4;                 // replay waves, and phases a tile's replay takes
-constexpr int kBwdWaves = kBwdReplay + 2;
+constexpr int kBwdWaves = kBwdReplay + 3;
 constexpr int kBwdBufs = kBwdReplay + 1;      // tiles whose weights are in LDS at a time
 constexpr int kBwdSteps = kTile / kBwdReplay; // steps a replay wave takes a phase
 constexpr int kBwdRing = 256;                 // Y columns in LDS: seven tiles and the lanes' skew
@@ -432,41 +433,48 @@ __global__ __launch_bounds__(kWave * kBwdWaves) void soft_bwd_kernel(SoftArgs a)
         load_tile(g0 - me);
         fill_ring(g0);
         team_barrier();
-        double left[RHO], upprev = INF, bot = INF;
-#pragma unroll
-        for (int r = 0; r < RHO; ++r) left[r] = INF;
-        for (int ph = -kBwdReplay;; ++ph) {
-          const int q = ph + 1 + ((me - ph - 1) & (kBwdReplay - 1));   // ph + 1 .. ph + 4
-          const int sub = ph - (q - kBwdReplay);
+        int ph = -kBwdReplay;
+        bool stop = false;
+        for (int w = 0; w < me && !stop; ++w, ++ph) {   // the waves start a phase after each other
+          team_barrier();
+          stop = uni(ctl[ph & 1]) != 0;
+        }
+        for (int q = me; !stop; q += kBwdReplay) {
           const int g = g0 - q;
-          if (q >= 0 && g >= g_lo) {
-            const int tg = 16 * g;
-            if (sub == 0) {
+          const int tg = 16 * g;
+          const int b = q % kBwdBufs;
+          const bool live = g >= g_lo;
+          const bool full = tg >= kWave - 1 && tg + kTile <= N;
+          double left[RHO];
 #pragma unroll
-              for (int r = 0; r < RHO; ++r) left[r] = st_n[r];
-              upprev = st_n[RHO];
-              bot = left[RHO - 1];
-              if (lane < kTile) bfw[me][lane] = has_above ? rf_n : INF;
-              __atomic_signal_fence(__ATOMIC_SEQ_CST);
-              __builtin_amdgcn_wave_barrier();
-              load_tile(g - kBwdReplay);   // in flight during this tile
+          for (int r = 0; r < RHO; ++r) left[r] = st_n[r];
+          double upprev = st_n[RHO];
+          double bot = left[RHO - 1];
+          if (lane < kTile) bfw[me][lane] = has_above ? rf_n : INF;
+          __atomic_signal_fence(__ATOMIC_SEQ_CST);
+          __builtin_amdgcn_wave_barrier();
+          load_tile(g - kBwdReplay);   // in flight during this tile
+          auto steps = [&](auto full_tag, int u0) {
+            constexpr bool FULL = decltype(full_tag)::value;
+            // the LDS operands of all four steps first: read next to their
+            // use, they cost a trip to LDS in every step's chain
+            const int yb = (tg + u0 - lane) & (kBwdRing - 1);   // ring slot of the first column
+            double bf[kBwdSteps], yy[kBwdSteps], y[kBwdSteps][D];
+#pragma unroll
+            for (int u = 0; u < kBwdSteps; ++u) {
+              bf[u] = bfw[me][u0 + u];
+              yy[u] = yq[yb + u];
+#pragma unroll
+              for (int c = 0; c < D; ++c) y[u][c] = ys[c][yb + u];
             }
-            const int u0 = sub * kBwdSteps;
-            const int yb = (tg + u0 - lane) & (kBwdRing - 1);   // ring slot of this phase's first column
-            const bool full = tg >= kWave - 1 && tg + kTile <= N;
-            const int b = q % kBwdBufs;
 #pragma unroll
             for (int u = 0; u < kBwdSteps; ++u) {
               const int j = tg + u0 + u - lane;
-              const double upin = shr1_f64(bot, bfw[me][u0 + u]);
+              const double upin = shr1_f64(bot, bf[u]);
               const double dgi = upprev;
               upprev = upin;
               float wu[RHO] = {}, wl[RHO] = {};
-              if (full || (j >= 0 && j < N)) {
-                double y[D];
-#pragma unroll
-                for (int c = 0; c < D; ++c) y[c] = ys[c][yb + u];
-                const double yy = yq[yb + u];
+              if (FULL || (j >= 0 && j < N)) {
                 double dg = dgi, up = upin;
                 const double bd0 = (double)ib * (double)(N - 1) - (double)j * (double)(M - 1);
 #pragma unroll
@@ -478,13 +486,13 @@ __global__ __launch_bounds__(kWave * kBwdWaves) void soft_bwd_kernel(SoftArgs a)
                     // cell receives and passes on exactly nothing
                     const bool inb = __builtin_fabs(bd0 + (double)r * (double)(N - 1)) <= band_b;
                     const SoftMin sm = softmin3_band(dg, up, lf, inb);
-                    rv = inb ? sq_cost<D>(xr[r], xx[r], y, yy) + sm.v : INF;
+                    rv = inb ? sq_cost<D>(xr[r], xx[r], y[u], yy[u]) + sm.v : INF;
                     const float rs = __builtin_amdgcn_rcpf(inb ? sm.s : 1.0f);
                     wu[r] = inb ? sm.eu * rs : 0.0f;
                     wl[r] = inb ? sm.el * rs : 0.0f;
                   } else {
                     const SoftMin sm = softmin3(dg, up, lf);
-                    rv = sq_cost<D>(xr[r], xx[r], y, yy) + sm.v;
+                    rv = sq_cost<D>(xr[r], xx[r], y[u], yy[u]) + sm.v;
                     const float rs = __builtin_amdgcn_rcpf(sm.s);   // s >= 1: the minimum's term is 1
                     wu[r] = sm.eu * rs;
                     wl[r] = sm.el * rs;
@@ -497,33 +505,33 @@ __global__ __launch_bounds__(kWave * kBwdWaves) void soft_bwd_kernel(SoftArgs a)
               }
               wb[b][u0 + u][lane] = make_float4(wu[0], wl[0], wu[1], wl[1]);
             }
+          };
+          for (int sub = 0; sub < kBwdReplay && !stop; ++sub, ++ph) {
+            if (live) {
+              if (full) steps(std::true_type{}, sub * kBwdSteps);
+              else steps(std::false_type{}, sub * kBwdSteps);
+            }
+            team_barrier();
+            stop = uni(ctl[ph & 1]) != 0;
           }
-          team_barrier();
-          if (uni(ctl[ph & 1])) break;
         }
       }
     } else {
       // ---- row sums, and the Y columns of later tiles
-      // float64 row accumulators: sum_j e and sum_j e (-2 y'_j)
-      double acc_e[RHO], acc_ey[RHO][D];
+      const int r = wv - (kBwdReplay + 1);   // the row of the lane this wave sums
+      // float64 accumulators: sum_j e and sum_j e (-2 y'_j)
+      double acc_e = 0.0, acc_ey[D];
 #pragma unroll
-      for (int r = 0; r < RHO; ++r) {
-        acc_e[r] = 0.0;
-#pragma unroll
-        for (int c = 0; c < D; ++c) acc_ey[r][c] = 0.0;
-      }
+      for (int c = 0; c < D; ++c) acc_ey[c] = 0.0;
       auto add_tile = [&](int g, int b) {   // cells outside the grid have e = 0 and y = 0
         const int yb = (16 * g - lane) & (kBwdRing - 1);
 #pragma unroll
         for (int u = kTile - 1; u >= 0; --u) {
-          const float2 e = eb[b][u][lane];
-          const double er[RHO] = {(double)e.x, (double)e.y};
+          const float2 ev = eb[b][u][lane];
+          const double e = r == 0 ? ev.x : ev.y;
+          acc_e += e;
 #pragma unroll
-          for (int r = RHO - 1; r >= 0; --r) {
-            acc_e[r] += er[r];
-#pragma unroll
-            for (int c = 0; c < D; ++c) acc_ey[r][c] = __builtin_fma(er[r], ys[c][yb + u], acc_ey[r][c]);
-          }
+          for (int c = 0; c < D; ++c) acc_ey[c] = __builtin_fma(e, ys[c][yb + u], acc_ey[c]);
         }
       };
       for (;;) {
@@ -538,8 +546,8 @@ __global__ __launch_bounds__(kWave * kBwdWaves) void soft_bwd_kernel(SoftArgs a)
         int ph = -kBwdReplay;
         for (;; ++ph) {
           const int q = ph + kBwdReplay + 1;   // the tile whose replay begins in the next phase
-          if (q >= kBwdReplay && lane < kTile) put_col(first_col(q), raw);
-          if (q + 1 >= kBwdReplay) get_col(first_col(q + 1), raw);
+          if (r == 0 && q >= kBwdReplay && lane < kTile) put_col(first_col(q), raw);
+          if (r == 0 && q + 1 >= kBwdReplay) get_col(first_col(q + 1), raw);
           if (ph >= 1) add_tile(g0 - (ph - 1), (ph - 1) & 1);
           team_barrier();
           if (uni(ctl[ph & 1])) break;
@@ -550,16 +558,13 @@ __global__ __launch_bounds__(kWave * kBwdWaves) void soft_bwd_kernel(SoftArgs a)
       // is (2 x' sum_j e + sum_j e (-2 y'_j)) / sk, and mass; the first
       // gradient row of this pair: per-cycle blocks of L rows, or the packed X rows
       const int64_t grow = a.rows_packed ? pd.x_off : (int64_t)pd.out * a.L;
+      const int i = ib + r;
+      if (i < M) {
+        const int64_t o = grow + i;
 #pragma unroll
-      for (int r = 0; r < RHO; ++r) {
-        const int i = ib + r;
-        if (i < M) {
-          const int64_t o = grow + i;
-#pragma unroll
-          for (int c = 0; c < D; ++c)
-            a.gsum[o * D + c] = (2.0 * xr[r][c] * acc_e[r] + acc_ey[r][c]) / sk;
-          a.hsum[o] = acc_e[r];
-        }
+        for (int c = 0; c < D; ++c)
+          a.gsum[o * D + c] = (2.0 * (r == 0 ? xr[0][c] : xr[1][c]) * acc_e + acc_ey[c]) / sk;
+        a.hsum[o] = acc_e;
       }
     }
     __syncthreads();
