@@ -387,6 +387,20 @@ int bwd_grid(const wts_plan* p, const PairSet& ps) {
   return std::max(1, std::min(g, ps.n_items));
 }
 
+// The Soft-DTW backward: a workgroup a strip (wts_soft_bwd.hip), or, where every
+// tile is swept and there are many strips, one wave a strip
+// (wts_soft_dense.hip).  Workgroup / wave, ms, d = 6: 8 strips a compute unit
+// (64 cycles of 4k) 3.3 / 3.5, 14 (512 of 800) 1.54 / 1.16, 32 (128 of 8k) 24.5 /
+// 16.9.
+bool bwd_by_waves(const wts_plan* p, const PairSet& ps) {
+  return p->opts.dense_e && ps.n_items > 10 * (int64_t)p->cus;
+}
+hipError_t run_soft_bwd(const wts_plan* p, const PairSet& ps, int dtype, const wts::SoftArgs& a,
+                        hipStream_t st) {
+  if (bwd_by_waves(p, ps)) return wts::launch_soft_bwd_dense(p->d, dtype, a, default_grid(p, ps), st);
+  return wts::launch_soft_bwd(p->d, dtype, a, bwd_grid(p, ps), st);
+}
+
 // Waves of a one-wave DTW sweep: the caller's, or ps.waves to a SIMD (four to
 // a workgroup, ps.waves workgroups to a compute unit).
 int dtw_grid(const wts_plan* p, const PairSet& ps) {
@@ -1024,7 +1038,7 @@ wts_status wts_softdtw_backward(const wts_plan* p, const double* bary, const voi
   a.zero_skip = p->opts.dense_e ? 0 : 1;
   a.tiles = p->d_tiles;
   const int tk = timing_begin(p, WTS_OP_SOFT_BWD, st);
-  HIP_TRY(wts::launch_soft_bwd(p->d, p->dtype, a, bwd_grid(p, ps), st));
+  HIP_TRY(run_soft_bwd(p, ps, p->dtype, a, st));
   timing_end(p, tk, st);
   HIP_TRY(wts::launch_soft_reduce(a.gsum, a.hsum, grad_value, p->n, p->L, p->d, grad_bary,
                                   row_mass, accumulate, st));
@@ -1075,7 +1089,7 @@ wts_status wts_softdtw_grad_cycles(const wts_plan* p, const double* bary, const 
   a.n_flags = ps.n_flags;
   a.zero_skip = p->opts.dense_e ? 0 : 1;
   a.tiles = p->d_tiles;
-  HIP_TRY(wts::launch_soft_bwd(p->d, WTS_F64, a, bwd_grid(p, ps), st));
+  HIP_TRY(run_soft_bwd(p, ps, WTS_F64, a, st));
   HIP_TRY(wts::launch_soft_rows_scale(a.gsum, p->d_off, p->n, p->off[p->n], p->d, grad_value,
                                       grad_cycles, st));
   return WTS_OK;
