@@ -56,11 +56,13 @@ HBM_PEAK_GBS = 8000.0
 # count 1, a transcendental counts tau; loads, LDS and cross-lane moves are
 # not counted, and neither is recomputation).
 
-def c_dba(d: int) -> int:
-    """DTW with a 2-bit argmin code per cell (the DBA path sweep): the value
-    recursion (d subtractions, 1 multiply, d-1 FMAs, 2 minima, 1 add) plus
-    the two comparisons that decide the code."""
-    return 2 * d + 5
+def c_dba(d: int, mode: int = 4) -> int:
+    """The DBA path sweep: the value recursion (d subtractions, 1 multiply,
+    d-1 FMAs, 2 minima, 1 add), and, when it keeps a 2-bit argmin code per
+    cell (mode 4), the two comparisons that decide it.  From checkpoints
+    (mode 2) only the cells near the paths are compared, which is
+    recomputation."""
+    return 2 * d + (5 if mode == 4 else 3)
 
 
 def c_score(d: int) -> int:
@@ -98,14 +100,16 @@ def c_soft_bwd(d: int, tau: float) -> float:
 
 def kernel_source_hash() -> str:
     h = hashlib.sha256()
-    for f in ("wts_sweep.h", "wts_dtw.hip", "wts_dtw32.hip", "wts_soft.hip", "wts_device.h"):
+    for f in ("wts_sweep.h", "wts_team.h", "wts_walk.h", "wts_trace.h", "wts_dtw.hip",
+              "wts_dtw32.hip", "wts_soft.h", "wts_soft.hip", "wts_soft_team.hip",
+              "wts_soft_bwd.hip", "wts_soft_dense.hip", "wts_device.h"):
         with open(os.path.join(ROOT, "paper_2404_12134_amd", "csrc", f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()[:16]
 
 
 KERNELS = {   # sweep -> rocprofv3 kernel name ({rho}: rows per lane of the plan;
-              # {mode}: the path sweep's mode, 2 without entry tags, 4 with them)
+              # {mode}: the path sweep's mode, 2 from checkpoints, 4 with codes and tags)
     "medoid": "void wts::(anonymous namespace)::dtw_fwd_kernel<float, float, double, 3, {rho}, 0, false>",
     "dba": "void wts::(anonymous namespace)::dtw_fwd_kernel<double, float, double, 3, {rho}, {mode}, false>",
     "score": "void wts::(anonymous namespace)::dtw_fwd_kernel<double, float, double, 3, {rho}, 1, false>",
@@ -386,8 +390,8 @@ def kname(key: str, rho: int, mode: int = 2) -> str:
 
 
 def path_mode(plan) -> int:
-    """The sweep mode of a barycenter plan's path sweep: 2 (codes only) when
-    it recovers paths pair by pair, 4 (with entry tags) strip by strip."""
+    """The sweep mode of a barycenter plan's path sweep: 2 (checkpoints) when
+    it recovers paths pair by pair, 4 (codes and entry tags) strip by strip."""
     return 2 if plan.walk() == "pairs" else 4
 
 
@@ -579,8 +583,8 @@ def c5_headline(wts, dev, steps: int, warmup: int, tau: float, gamma: float = 0.
     # the backward sweeps only the tiles whose E entries are not all zero:
     # its algorithmic work is that of the swept share of the cells
     kern = {   # name: (seconds per step, launches, cells, floor, KERNELS key, rho, mode)
-        "dba_path_sweep": (dba_s, 1, cells, c_dba(d), "c5_dba", plan.rho(wts.OP_DBA),
-                           path_mode(plan)),
+        "dba_path_sweep": (dba_s, 1, cells, c_dba(d, path_mode(plan)), "c5_dba",
+                           plan.rho(wts.OP_DBA), path_mode(plan)),
         "soft_fwd": (sum(fwd), len(groups), cells, c_soft_fwd(d, tau), "c5_soft_fwd", 2, 0),
         "soft_bwd": (sum(bwd), len(groups), cells * swept, c_soft_bwd(d, tau), "c5_soft_bwd", 2,
                      0),
@@ -725,15 +729,15 @@ def fp32_dba_compare(wts, plan, off, d, dt, L, Y, B, arena, cells, sec, t_dba):
         torch.cuda.synchronize()
         ms, nl = p32.sweep_ms(wts.OP_DBA)
         p32.check()
-        tried[(rho, grid)] = (ms / nl / 1e3, e0.elapsed_time(e1) / 1e3)
+        tried[(rho, grid)] = (ms / nl / 1e3, e0.elapsed_time(e1) / 1e3, path_mode(p32))
         if best is None or tried[(rho, grid)][1] < tried[best][1]:
             best = (rho, grid)
         if best == (rho, grid):
             sc32, d32, l32 = wts.anomaly_score(p32, B, Y)
         p32.close()
     torch.cuda.synchronize()
-    sweep_s, iter_s = tried[best]
-    ops = cells * c_dba(d)
+    sweep_s, iter_s, mode = tried[best]
+    ops = cells * c_dba(d, mode)
     ach = ops / sweep_s / 1e12
     peak = VALU_LANE_OPS_PEAK_F32 / 1e12
     d64h, d32h = out64[2].cpu().numpy(), out32[2].cpu().numpy()
@@ -745,7 +749,7 @@ def fp32_dba_compare(wts, plan, off, d, dt, L, Y, B, arena, cells, sec, t_dba):
         "dba_iteration_s": round(iter_s, 4), "dba_gcups": round(cells / iter_s / 1e9, 2),
         "path_sweep": {"bound": "alu", "achieved": round(ach, 3), "peak": round(peak, 3),
                        "unit": "TOP/s", "frac": round(ach / peak, 4),
-                       "launch_ms": round(sweep_s * 1e3, 3), "ops_per_cell": c_dba(d)},
+                       "launch_ms": round(sweep_s * 1e3, 3), "ops_per_cell": c_dba(d, mode)},
         "fp64_dba_iteration_s": round(t_dba, 4),
         "s_per_iteration_with_fp32_dba": round(sec - t_dba + iter_s, 4),
         "vs_fp64": {
@@ -880,7 +884,7 @@ def c2_section(wts, dev, steps: int = 3, speedup: bool = True):
     t_dba = float(np.mean(times["dba"])) / iters
     t_score = float(np.mean(times["score"]))
     sweeps = {"medoid": (mplan, wts.OP_MEDOID, cells_medoid, c_medoid(w.d)),
-              "dba": (plan, wts.OP_DBA, cells_bary, c_dba(w.d)),
+              "dba": (plan, wts.OP_DBA, cells_bary, c_dba(w.d, path_mode(plan))),
               "score": (plan, wts.OP_SCORE, cells_bary, c_score(w.d))}
     per = {}
     for key, (pl, op, cells, cm) in sweeps.items():
@@ -952,7 +956,7 @@ def c3_section(wts, dev, iters: int = 10, speedup: bool = True):
     it_s = e0.elapsed_time(e1) / 1e3 / iters
     del runner
     speed = dba_per_cycle_speedup(wts, plan, off, w.d, dt, w.L, Y, B0) if speedup else None
-    cm = c_dba(w.d)
+    cm = c_dba(w.d, path_mode(plan))
     rho = plan.rho(wts.OP_DBA)
     rf = roofline("c5_dba", rho, cells * cm * cnt, tot / 1e3, cnt, cells * cnt, cm,
                   name=kname("c5_dba", rho, path_mode(plan)))

@@ -72,10 +72,11 @@ def store_cache(path: str, key: str, entry: dict) -> None:
 
 
 def grid_candidates(op: str, cus: int) -> Tuple[int, ...]:
-    """Persistent sweep waves to try: 0 is the library's default (24 per
-    compute unit); fewer waves leave each SIMD fewer strips to interleave but
-    start fewer strips that then wait on their neighbours.  The Soft-DTW
-    backward holds three waves per SIMD (12 per compute unit)."""
+    """Persistent sweep waves to try: 0 is the library's default (for the DTW
+    sweeps chosen by the batch, for the Soft-DTW forward 24 per compute unit);
+    fewer waves leave each SIMD fewer strips to interleave but start fewer
+    strips that then wait on their neighbours.  A set value also keeps batches
+    of few strips with the one-wave sweeps."""
     if op == "soft":
         return (0, 12 * cus, 6 * cus)
     return (0, 16 * cus, 8 * cus)

@@ -13,14 +13,15 @@
 //    row over through device memory.  The DTW sweeps give every strip its own
 //    row, filled with a sentinel before the launch: the strip below polls
 //    the values themselves (device-scope loads) until no sentinel is left,
-//    so the producer needs neither a counter nor a store drain.  The
-//    Soft-DTW sweeps publish a per-strip progress counter (columns written
-//    so far) after their device-scope row stores, ordered by s_waitcnt; in
-//    both cases no L2 writeback is needed;
-//  * workgroups pop (pair, strip) items from a queue in which the strips of
-//    one pair are consecutive and pairs are sorted by decreasing size: a
-//    strip only ever waits for an item popped earlier by a running
-//    workgroup, so the sweep cannot deadlock.
+//    so the producer needs neither a counter nor a store drain; the team
+//    forward of Soft-DTW does the same.  The other Soft-DTW sweeps publish
+//    per-strip words (columns written so far; the backward also where its
+//    non-zero pushes begin and end) after their device-scope row stores,
+//    ordered by s_waitcnt; in no case is an L2 writeback needed;
+//  * workgroups pop (pair, strip) items from a queue ordered by the length of
+//    the chain each strip heads, in which every strip comes after the one it
+//    waits for: a strip only ever waits for an item popped earlier by a
+//    running workgroup, so the sweep cannot deadlock.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -37,7 +38,7 @@ struct PairDesc {
   int32_t M, N;       // rows of X, columns (samples of Y)
   int32_t S;          // strips
   int32_t out;        // output slot (cycle index, or pair index for the medoid)
-  int32_t flag_base;  // progress counter of strip 0
+  int32_t flag_base;  // progress word of strip 0
   int32_t WT;         // 16-step groups of a strip's sweep: ceil((N + 63) / 16), even for the DTW sweeps
   int32_t item_base;  // index of this pair's strip 0 in the item list
   int32_t pad;

@@ -23,9 +23,9 @@
 // where w_s(i, j) = 2^(m_s - r'(i, j)) / sum_s is the normalised weight of
 // (i, j) in the soft-min of its successor s, and e(M-1, N-1) = 1 (the cell
 // that closes the path).  The kernel walks each strip's tiles from the last
-// column to the first: it replays the tile forward, keeping the normalised
-// weights of the up and left predecessors of every cell in registers
-// (float32), then sweeps the tile backwards in "push" form -- each finished
+// column to the first: some waves replay the tiles forward, leaving the
+// normalised weights of the up and left predecessors of every cell in LDS
+// (float32), another sweeps each tile backwards in "push" form -- each finished
 // cell splits its e over its three predecessors with its own weights, the
 // diagonal taking what the other two do not, so that the split conserves e
 // up to the rounding of one float32 subtraction -- and no cell ever needs a

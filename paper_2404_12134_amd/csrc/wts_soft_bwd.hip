@@ -20,7 +20,9 @@ namespace {
 // strip above only after 63 + 128 steps (the lanes' skew and the columns a path
 // moves in 128 rows), so a tile's time counts twelve times a strip.  One wave
 // that replayed, pushed and summed its tiles in turn took 5.5 to 7 us a tile;
-// a phase takes about a fifth of it.
+// a phase takes 1.0 to 1.3 us, four steps of replay (2400 cycles) or the push
+// sweep (2200).  128 cycles of 20k (d = 6) 14.8 -> 4.8 ms, 5 of 18k (d = 1)
+// 10.7 -> 3.5 ms, 16 of 2k (d = 3) 1.30 -> 0.42 ms.
 constexpr int kBwdReplay = 4;                 // replay waves, and phases a tile's replay takes
 constexpr int kBwdWaves = kBwdReplay + 3;
 constexpr int kBwdBufs = kBwdReplay + 1;      // tiles whose weights are in LDS at a time

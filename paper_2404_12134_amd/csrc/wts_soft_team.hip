@@ -10,6 +10,8 @@
 // the strip below polls the values themselves, 16 at a time, where the
 // one-wave sweep announces whole chunks of 64 columns one chunk late: the
 // strips of a pair follow each other by about 110 steps instead of 220.
+// A step takes 121 to 138 ns, bound by that chain: 5 cycles of 18k in the 0.6
+// band 9.4 -> 4.7 ms, 16 of 2k (d = 3) 0.98 -> 0.44 ms.
 // The operations of a cell and what is left in the checkpoint buffer are
 // those of the one-wave sweep.
 #include "wts_soft.h"

@@ -1,6 +1,7 @@
 // wts_sweep.h -- the DTW wavefront sweep of gfx950 (value, value + path
 // length, checkpoints, argmin codes, Sub-DTW) and its launchers, shared by the float64
-// instances (wts_dtw.hip) and the float32-decision instances (wts_dtw32.hip).
+// instances (wts_dtw.hip) and the float32-decision instances (wts_dtw32.hip); one
+// wave a strip (batches of few strips: wts_team.h).
 //
 // The recurrence (Eq. 5 with gamma = 0, i.e. Eq. 1 by dynamic programming):
 //   r(-1,-1) = 0, r(i,-1) = r(-1,j) = +inf,
