@@ -80,6 +80,15 @@ __device__ __forceinline__ T ld_row(__amdgpu_buffer_rsrc_t r, int byte_off) {
     return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, byte_off, 0, 16));
 }
 
+// Tag of the cells outside the grid in row i: left of the first column, or above
+// the first row (i = -1).  DIST_LEN: a tag is the path length less the cell's
+// row, which an up or a diagonal move leaves as it is and a left move raises by
+// one; outside the grid the length is 0.  A path reaches these cells at (-1, -1)
+// alone, unless a cost overflows: where all three predecessors are +inf the
+// diagonal is taken, off the grid too, and the length counts the cells inside it.
+template <int MODE>
+__device__ __forceinline__ int border_tag(int i) { return MODE == MODE_DIST_LEN ? -i : 0; }
+
 // Waves per sweep workgroup.  Each wave works alone (own items, own LDS);
 // grouping four of them makes the dispatcher place one wave on each SIMD of a
 // compute unit, which one-wave workgroups do not get reliably.
@@ -172,18 +181,16 @@ void dtw_fwd_kernel(FwdArgs a) {
     int lx[RHO];
     uint32_t accd[RHO], accu[RHO];   // code planes: diagonal chosen; up not above left
 #pragma unroll
-    for (int r = 0; r < RHO; ++r) { left[r] = INF; lx[r] = 0; accd[r] = accu[r] = 0u; }
+    for (int r = 0; r < RHO; ++r) { left[r] = INF; lx[r] = border_tag<MODE>(ib + r); accd[r] = accu[r] = 0u; }
     TC upprev = (s == 0 && lane == 0) ? (TC)0 : INF;   // r(-1,-1) = 0 at the origin
     // Sub-DTW: running minimum of the last row (lowest column on ties)
     const bool last_strip = s + 1 == pd.S;
     const int rl_last = M - 1 - ib;
     TC sub_best = INF;
     int sub_end = 0, sub_start = 0;
-    // DIST_LEN: the tag is the path length less the cell's row, which an up or a
-    // diagonal move leaves as it is and a left move raises by one
-    int upprevx = MODE == MODE_DIST_LEN ? 1 : 0;
+    int upprevx = border_tag<MODE>(ib - 1);
     TC bot = INF;
-    int botx = 0;
+    int botx = border_tag<MODE>(ib + RHO - 1);
     bool gave_up = false;   // set once a wait times out: the strip never waits again
 
     // The strip above's bottom row, 16 columns at a time: lanes 0..15 hold the
@@ -410,7 +417,7 @@ void dtw_fwd_kernel(FwdArgs a) {
         if (lane < 16) {   // this group's upper input, ready and checked
           // above the first strip: +inf, or 0 for Sub-DTW (free start)
           binr[lane] = has_prev ? (tg + lane < N ? pr : INF) : (MODE == MODE_SUB ? (TC)0 : INF);
-          if (kAux) binx[lane] = has_prev ? px : 0;
+          if (kAux) binx[lane] = has_prev ? px : border_tag<MODE>(-1);
         }
         wave_sync();
         if (tg > 0) publish(tg - 16);

@@ -74,13 +74,11 @@ __global__ __launch_bounds__(kWave * kTeamWaves) void dtw_team_kernel(FwdArgs a)
       int lx[RHO];
       uint32_t accd[RHO], accu[RHO];
 #pragma unroll
-      for (int r = 0; r < RHO; ++r) { left[r] = INF; lx[r] = 0; accd[r] = accu[r] = 0u; }
+      for (int r = 0; r < RHO; ++r) { left[r] = INF; lx[r] = border_tag<MODE>(ib + r); accd[r] = accu[r] = 0u; }
       TC upprev = (s == 0 && lane == 0) ? (TC)0 : INF;   // r(-1,-1) = 0 at the origin
-      // DIST_LEN: the tag is the path length less the cell's row, which an up
-      // or a diagonal move leaves as it is and a left move raises by one
-      int upprevx = MODE == MODE_DIST_LEN ? 1 : 0;
+      int upprevx = border_tag<MODE>(ib - 1);
       TC bot = INF;
-      int botx = 0;
+      int botx = border_tag<MODE>(ib + RHO - 1);
       const bool last_strip = s + 1 == pd.S;
       const int rl_last = M - 1 - ib;
       TC sub_best = INF;
@@ -268,7 +266,7 @@ __global__ __launch_bounds__(kWave * kTeamWaves) void dtw_team_kernel(FwdArgs a)
         if (lane < G) {
           // above the first strip: +inf, or 0 for Sub-DTW (free start)
           binr[g & 1][lane] = has_prev ? (j < N ? pr : INF) : (MODE == MODE_SUB ? (TC)0 : INF);
-          if (kAux) binx[g & 1][lane] = has_prev ? px : 0;
+          if (kAux) binx[g & 1][lane] = has_prev ? px : border_tag<MODE>(-1);
         }
       };
       load_cols(0);
