@@ -15,7 +15,9 @@
 #include "../../include/wetsand_mi.h"
 #include "wts_kernels.h"
 #include "wts_order.h"
+#include "wts_rules.h"
 
+using namespace wts::rules;
 using wts::PairDesc;
 
 namespace {
@@ -39,9 +41,6 @@ wts_status fail(wts_status st, const char* fmt, ...) {
     if (e_ != hipSuccess)                                                                 \
       return fail(WTS_E_HIP, "%s failed: %s", #call, hipGetErrorString(e_));              \
   } while (0)
-
-constexpr size_t kAlign = 256;
-size_t align_up(size_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
 
 // Pairs of one kind (barycenter vs cycles, or cycle vs cycle) with their
 // sweep items and the sizes of the buffers the sweep needs.
@@ -67,17 +66,6 @@ struct Job {
   int64_t x_off, y_off;
   int32_t M, N, out;
 };
-
-// Strip row stride of the DTW sweeps (row_stride in wts_sweep.h).
-int64_t row_stride_host(int32_t N) { return (N + wts::kWave - 1 + 3) & ~3; }
-
-// Workspace of a score sweep with that many strip row elements (the layout of
-// WTS_OP_SCORE).
-size_t score_bytes(int64_t rows, int n) {
-  return align_up(2 * sizeof(int)) + align_up(sizeof(double) * (size_t)rows) +
-         align_up(sizeof(int) * (size_t)rows) + align_up(sizeof(double) * (size_t)n) +
-         align_up(sizeof(int) * (size_t)n);
-}
 
 void build_set(PairSet& ps, std::vector<Job> jobs, int rho, bool soft) {
   const int H = wts::kWave * rho;
@@ -152,64 +140,9 @@ struct Layout {
 // the process ends.  Host code never uses the array's name as an address:
 // wts_plan_create resolves the device address once per GPU (with that GPU
 // current) into g_scratch.
-constexpr size_t kScratchBytes = size_t(32) << 20;
 constexpr int kMaxDevices = 64;
 std::mutex g_scratch_mu;
 void* g_scratch[kMaxDevices] = {};
-
-// Whether a set of `items` strips is swept by teams of four waves a strip
-// (wts_team.h) or by one wave a strip.  Teams win while the strips leave
-// compute units or SIMDs idle.  Score sweep / DBA iteration in us, team
-// against one wave, float64, d = 3: 8 x 4.4k (L = 4000) 559 / 736 against
-// 931 / 1136, 32 x 4.4k 761 / 903 against 957 / 1161; past five strips of two
-// rows a lane per compute unit the two are even (48 x 4.4k: 961 / 1128 against
-// 968 / 1168), and at seven the team loses (16 x 16k: 3941 / 4456 against
-// 3599 / 4321).  Teams of four rows a lane hold 64 KB of LDS (float64), two a
-// compute unit, and win up to that; in float32 they hold half of it.
-bool team_pays(int rho, int64_t items, int cus, bool fp32) {
-  if (rho == 2) return items <= 5 * (int64_t)cus;
-  return rho == 4 && items <= (fp32 ? 4 : 2) * (int64_t)cus;
-}
-
-// The Soft-DTW forward: teams of four waves a strip (wts_soft_team.hip) or one
-// wave a strip.  A team takes half the time a step and follows the strip above
-// at half the distance; one wave a strip has fewer instructions a cell once
-// the SIMDs are full.  Team against one wave, ms: 16 x 2k (256 strips, d = 3)
-// 0.44 / 0.98, 5 x 18k 4.3 / 9.4, 25 x 18k (3600 strips) 10.0 / 14.9, 100 x 8k
-// (6300 strips) 6.8 / 8.3 and at d = 6 8.7 / 9.1, 400 x 2k (6400) 1.77 / 2.01
-// and at d = 6 2.27 / 2.23, 200 x 8k (12,600) 12.4 / 12.9 and at d = 6 16.3 /
-// 14.6.
-bool soft_team_pays(int64_t items, int cus) { return items <= 24 * (int64_t)cus; }
-
-// Rows per lane of the barycenter sweeps when the caller leaves it open.
-// Batches of few strips take 2 and are swept by teams (in float32 above four
-// such strips a compute unit, teams of 4: 16 x 16k, d = 3, score / DBA 2526 /
-// 2973 us against 2746 / 3431).  Others take 4, with one wave to a SIMD and
-// one workgroup to a compute unit up to 1024 strips.  Float64 batches of two
-// channels or more and of more than four strips a SIMD take 5 where the
-// padding of the last strip allows it: a step costs about 2 d + 4
-// instructions a row and 10 of its own, which 5 rows share (40 cycles of
-// 40k-50k samples, d = 6, score / checkpointed sweep: 74.3 / 61.2 ms against
-// 77.7 / 64.8; 25 of 30k: 22.9 / 19.2 against 20.6 / 18.2).  In float32 the
-// score sweep is no faster at 5.  Up to four strips a SIMD the longest pair's
-// chain (120 steps a strip) or the rounds of strips on the SIMDs decide, at
-// about 2 d + 8 instructions a row and 20 a step: 5 rows a lane win where they
-// save a strip or a round (500 cycles of 300, L = 300, one strip instead of
-// two: 72 against 85 us).
-int bary_rho(int64_t L, int n, int64_t nmax, int cus, int d, bool fp32, bool team) {
-  auto strips = [&](int r) { return (L + 64 * r - 1) / (64 * r); };
-  auto items = [&](int r) { return (int64_t)n * strips(r); };
-  const int64_t simds = 4 * (int64_t)cus;
-  if (team && fp32 && items(2) > simds && team_pays(4, items(4), cus, fp32)) return 4;
-  if (team && team_pays(2, items(2), cus, fp32)) return 2;
-  auto steps = [&](int r) { return strips(r) * (r * (2 * d + 4) + 10); };
-  if (items(4) > 4 * simds) return d >= 2 && !fp32 && steps(5) < steps(4) ? 5 : 4;
-  auto chain = [&](int r) {
-    const int64_t rounds = (items(r) + simds - 1) / simds, one = nmax + wts::kWave;
-    return std::max(one + 120 * strips(r), rounds * one) * (r * (2 * d + 8) + 20);
-  };
-  return chain(5) * 100 < chain(4) * 97 ? 5 : 4;
-}
 
 // Waves per SIMD of the one-wave sweeps.  A second wave on a SIMD raises its
 // throughput (a step of both takes 1.67 times a step of one in float64, 1.3
@@ -648,18 +581,7 @@ wts_status wts_plan_create(wts_plan** out, int device, int32_t n, int32_t d, int
       jobs.push_back(Job{0, p->off[k], (int32_t)L, (int32_t)(p->off[k + 1] - p->off[k]), k});
     const bool fp32 = o.decision == WTS_DECISION_FP32;
     const bool team = o.grid == 0;   // a grid asks for that many one-wave sweepers
-    int rho = o.rho ? o.rho : bary_rho(L, n, p->nmax, p->cus, d, fp32, team);
-    // more rows a lane leave fewer strip rows: a batch whose score workspace
-    // fits the scratch of wts_anomaly_score_noalloc only with those of the
-    // one-wave sweeps keeps them
-    auto scratch_fits = [&](int r) {
-      int64_t rows = 0;
-      for (const Job& jb : jobs)
-        rows += (int64_t)((jb.M + wts::kWave * r - 1) / (wts::kWave * r)) * row_stride_host(jb.N);
-      return score_bytes(rows, n) <= kScratchBytes;
-    };
-    const int alt = o.rho ? rho : bary_rho(L, n, p->nmax, p->cus, d, fp32, false);
-    if (alt != rho && !scratch_fits(rho) && scratch_fits(alt)) rho = alt;
+    const int rho = o.rho ? o.rho : plan_rho(p->off.data(), n, L, p->cus, d, fp32, team);
     build_set(p->bary, jobs, rho, false);
     p->bary.team = team && team_pays(p->bary.rho, p->bary.n_items, p->cus, fp32);
     p->bary.waves = sweep_waves(p->bary, p->cus, d, fp32, false);

@@ -1,0 +1,28 @@
+// Rows per lane and score workspace of barycenter plans (wts_rules.h), read from
+// stdin: d L fp32 team cus n, then n cycle lengths -> "rho bytes2 bytes4 bytes5".
+#include <cstdio>
+#include <vector>
+
+#include "wts_rules.h"
+
+int main() {
+  using namespace wts::rules;
+  int d, fp32, team, cus, n;
+  long long L, len;
+  while (std::scanf("%d %lld %d %d %d %d", &d, &L, &fp32, &team, &cus, &n) == 6) {
+    std::vector<int64_t> off(1, 0);
+    for (int k = 0; k < n; ++k) {
+      if (std::scanf("%lld", &len) != 1) return 2;
+      off.push_back(off.back() + len);
+    }
+    std::printf("%d", plan_rho(off.data(), n, L, cus, d, fp32 != 0, team != 0));
+    for (int r : {2, 4, 5}) {
+      int64_t rows = 0;
+      for (int k = 0; k < n; ++k)
+        rows += (L + kLanes * r - 1) / (kLanes * r) * row_stride_host((int32_t)(off[k + 1] - off[k]));
+      std::printf(" %zu", score_bytes(rows, n));
+    }
+    std::printf("\n");
+  }
+  return 0;
+}

@@ -1,0 +1,67 @@
+"""The rows per lane a barycenter plan takes (csrc/wts_rules.h), built with the
+host compiler: a plan whose score workspace fitted the scratch of the
+non-allocating score entry point with the rows of the earlier rule (4, or 5
+where that brings more than 13/16 of the SIMDs' strips under it) still fits."""
+import os
+import shutil
+import subprocess
+
+import numpy as np
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+CSRC = os.path.join(HERE, "..", "paper_2404_12134_amd", "csrc")
+SCRATCH = 32 << 20
+CUS = 256
+
+
+@pytest.fixture(scope="module")
+def rules_bin(tmp_path_factory):
+    cxx = shutil.which("g++") or shutil.which("c++")
+    if cxx is None:
+        pytest.skip("no host C++ compiler")
+    exe = str(tmp_path_factory.mktemp("rules") / "rules")
+    subprocess.run([cxx, "-std=c++17", "-O1", "-I", CSRC, os.path.join(HERE, "rules_main.cpp"),
+                    "-o", exe], check=True)
+    return exe
+
+
+def plans(exe, cases):
+    """[(d, L, fp32, team, lengths)] -> [(rho, {rho: workspace bytes})]"""
+    inp = "\n".join("%d %d %d %d %d %d %s" % (d, L, fp32, team, CUS, len(lens),
+                                             " ".join(map(str, lens)))
+                    for d, L, fp32, team, lens in cases)
+    out = subprocess.run([exe], input=inp, capture_output=True, text=True, check=True).stdout
+    rows = [tuple(map(int, ln.split())) for ln in out.splitlines()]
+    return [(r[0], dict(zip((2, 4, 5), r[1:]))) for r in rows]
+
+
+def earlier_rho(L, n):
+    simds = 4 * CUS
+    i4, i5, cap = n * -(-L // 256), n * -(-L // 320), simds * 13 // 16
+    return 5 if cap < i4 <= 2 * simds and i5 <= cap else 4
+
+
+def test_plans_at_the_border_of_the_scratch(rules_bin):
+    got = plans(rules_bin, [(3, 17560, 0, 1, [3000] * 14), (3, 3072, 0, 1, [3000] * 83)])
+    for rho, size in got:
+        assert size[5] <= SCRATCH < size[4] and rho == 5
+
+
+@pytest.mark.parametrize("fp32", [0, 1])
+@pytest.mark.parametrize("team", [0, 1])
+def test_no_plan_that_fitted_the_scratch_is_refused(rules_bin, team, fp32):
+    rng = np.random.default_rng(2 * team + fp32)
+    cases = []
+    for _ in range(6000):
+        n = int(np.exp(rng.uniform(0, np.log(600))))
+        L = int(np.exp(rng.uniform(0, np.log(50000))))
+        N = int(np.exp(rng.uniform(0, np.log(50000))))
+        lens = [N] * n if rng.random() < 0.5 else rng.integers(max(1, N // 2), 2 * N, n).tolist()
+        cases.append((int(rng.integers(1, 9)), L, fp32, team, lens))
+    lost = fitted = 0
+    for (d, L, _, _, lens), (rho, size) in zip(cases, plans(rules_bin, cases)):
+        if size[earlier_rho(L, len(lens))] <= SCRATCH:
+            fitted += 1
+            lost += size[rho] > SCRATCH
+    assert fitted > 1000 and lost == 0
