@@ -176,14 +176,14 @@ __global__ __launch_bounds__(kWave * kBwdWaves) void soft_bwd_kernel(SoftArgs a)
         return __builtin_amdgcn_ballot_w64(p) != 0;
       };
       // waits until *word satisfies ok, and returns it (uniform); 0 after a timeout
-      auto wait_word = [&](const int* word, auto ok) {
+      auto wait_word = [&](const int* word, int limit, auto ok) {
         int got = 0, quit = 0;
         if (lane == 0) {
           int polls = 0;
           got = ld_dev(word);
           while (!ok(got)) {
             if (polls > 4) poll_backoff(polls, 0);
-            if (++polls > kSpinLimit) {
+            if (++polls > limit) {
               atomicOr(a.status, kStatusSpinTimeout);
               quit = 1;
               break;
@@ -196,10 +196,13 @@ __global__ __launch_bounds__(kWave * kBwdWaves) void soft_bwd_kernel(SoftArgs a)
         __atomic_signal_fence(__ATOMIC_SEQ_CST);
         return r;
       };
-      // the place where the input begins
+      // the place where the input begins.  The strips below may sweep or pass over
+      // every tile of the pair before they push anything up (their tiles until
+      // then cover each column once, and five more a strip), a microsecond or two
+      // a tile, about a poll: two seconds for 2^24 columns.
       auto learn_start = [&]() {
         if (in_known || gave_up) return;
-        const int w = wait_word(below.start, [](int v) { return v != 0; });
+        const int w = wait_word(below.start, kSpinLimit + 32 * (G + 16 * pd.S), [](int v) { return v != 0; });
         in_known = true;
         in_hi = w > 0 ? min(16 * (w - 1) + kTile - 1, N - 1) : -1;
         if (w <= 0) { in_done = true; seen_below = N; }   // no input at all
@@ -215,7 +218,7 @@ __global__ __launch_bounds__(kWave * kBwdWaves) void soft_bwd_kernel(SoftArgs a)
       auto wait_below = [&](int jlo) {
         const int need = N - max(0, jlo);
         if (need > seen_below && !gave_up)
-          seen_below = wait_word(below.prog, [&](int v) { return v >= need; });
+          seen_below = wait_word(below.prog, kSpinLimit, [&](int v) { return v >= need; });
         learn_end();
       };
       // the pushes into columns [c, c + 64) of the bottom row, a column a lane
