@@ -27,7 +27,7 @@ SOURCES = {"wts_dtw.hip": ["-fno-honor-nans"], "wts_dtw32.hip": ["-fno-honor-nan
            "wts_team32.hip": ["-fno-honor-nans"],
            "wts_trace.hip": ["-fno-honor-nans"], "wts_trace32.hip": ["-fno-honor-nans"],
            "wts_soft.hip": ["-fno-honor-nans"], "wts_soft_bwd.hip": ["-fno-honor-nans"],
-           "wts_soft_team.hip": ["-fno-honor-nans"], "wts_soft_dense.hip": ["-fno-honor-nans"],
+           "wts_soft_team.hip": ["-fno-honor-nans"], "wts_soft_wave.hip": ["-fno-honor-nans"],
            "wts_abi.hip": [], "wts_aux.hip": []}
 ARCH = os.environ.get("WTS_OFFLOAD_ARCH", "gfx950")
 

@@ -56,6 +56,9 @@ struct PairSet {
   int n_pairs = 0, n_items = 0, n_flags = 0;
   int64_t code_words = 0, bnd_elems = 0, aux_strip_elems = 0, state_elems = 0, row_elems = 0;
   int64_t max_rows = 0;
+  int64_t tiles = 0;         // 16-step tiles of all strips
+  int max_strips = 0;        // of a pair
+  double live_most = 0.0;    // live tiles a strip can have, about
   int rho = 4;   // barycenter rows per lane of this set's sweeps
   int waves = 1;             // one-wave sweeps: waves per SIMD
   bool team = false;         // swept by teams of four waves a strip
@@ -105,6 +108,9 @@ void build_set(PairSet& ps, std::vector<Job> jobs, int rho, bool soft) {
     for (int s = 0; s < d.S; ++s) ps.items.push_back(make_int2((int)p, s));
     ps.pairs.push_back(d);
     ps.max_rows = std::max<int64_t>(ps.max_rows, jb.M);
+    ps.tiles += (int64_t)d.S * d.WT;
+    ps.max_strips = std::max(ps.max_strips, d.S);
+    ps.live_most = std::max(ps.live_most, bwd_live_most(jb.M, jb.N));
   }
   std::vector<int64_t> cols(ps.pairs.size());
   std::vector<int> strips(ps.pairs.size());
@@ -227,7 +233,7 @@ Layout layout(const wts_plan* p, int op) {
                       : op == WTS_OP_SOFT_GRAD_C ? p->softT : p->bary;
   if (op == WTS_OP_SOFT_GRAD_C) {   // the transposed forward and backward in one buffer
     const int64_t rows = p->off[p->n];
-    l.queue = take(2 * sizeof(int));
+    l.queue = take(wts::kQueueWords * sizeof(int));
     l.progress = take(3 * sizeof(int) * (size_t)ps.n_flags);
     l.rows = take(sizeof(double) * (size_t)ps.aux_strip_elems);
     l.states = take(sizeof(double) * (size_t)ps.state_elems);
@@ -240,7 +246,7 @@ Layout layout(const wts_plan* p, int op) {
     return l;
   }
   if (op == WTS_OP_SOFT_FWD || op == WTS_OP_SOFT_BWD) {
-    l.queue = take(2 * sizeof(int));
+    l.queue = take(wts::kQueueWords * sizeof(int));
     l.progress = take((op == WTS_OP_SOFT_FWD ? 1 : 3) * sizeof(int) * (size_t)ps.n_flags);
     if (op == WTS_OP_SOFT_FWD) {
       l.rows = take(sizeof(double) * (size_t)ps.aux_strip_elems);
@@ -320,18 +326,27 @@ int bwd_grid(const wts_plan* p, const PairSet& ps) {
   return std::max(1, std::min(g, ps.n_items));
 }
 
-// The Soft-DTW backward: a workgroup a strip (wts_soft_bwd.hip), or, where every
-// tile is swept and there are many strips, one wave a strip
-// (wts_soft_dense.hip).  Workgroup / wave, ms, d = 6: 8 strips a compute unit
-// (64 cycles of 4k) 3.3 / 3.5, 14 (512 of 800) 1.54 / 1.16, 32 (128 of 8k) 24.5 /
-// 16.9.
-bool bwd_by_waves(const wts_plan* p, const PairSet& ps) {
-  return p->opts.dense_e && ps.n_items > 10 * (int64_t)p->cus;
+// Waves of its one-wave form: three to a SIMD, the most its registers allow.
+int wave_grid(const wts_plan* p, const PairSet& ps) {
+  const int g = p->opts.grid > 0 ? p->opts.grid : 12 * p->cus;
+  return std::max(1, std::min(g, ps.n_items));
 }
-hipError_t run_soft_bwd(const wts_plan* p, const PairSet& ps, int dtype, const wts::SoftArgs& a,
+
+// The Soft-DTW backward: by workgroups or by waves (bwd_wave_tiles).  Where every
+// tile is swept the live tiles are known; else they depend on the values and on
+// gamma.  Below any E's width the waves take the batch, above the widest the
+// workgroups do; in between the workgroups begin, and hand the rest of the queue
+// to the waves once their strips turn out that wide.  The bits are the same.
+hipError_t run_soft_bwd(const wts_plan* p, const PairSet& ps, int dtype, wts::SoftArgs a,
                         hipStream_t st) {
-  if (bwd_by_waves(p, ps)) return wts::launch_soft_bwd_dense(p->d, dtype, a, default_grid(p, ps), st);
-  return wts::launch_soft_bwd(p->d, dtype, a, bwd_grid(p, ps), st);
+  constexpr int kNarrow = 14;   // live tiles a strip has at least, about
+  const int w = bwd_wave_tiles(ps.n_items, ps.max_strips, p->cus, p->d);
+  if (p->opts.dense_e ? (double)ps.tiles >= (double)w * ps.n_items : w <= kNarrow)
+    return wts::launch_soft_bwd_wave(p->d, dtype, a, default_grid(p, ps), st);
+  a.wave_tiles = p->opts.dense_e || w > ps.live_most || ps.n_items > (1 << 29) ? 0 : w;
+  const hipError_t e = wts::launch_soft_bwd(p->d, dtype, a, bwd_grid(p, ps), st);
+  if (e != hipSuccess || a.wave_tiles == 0) return e;
+  return wts::launch_soft_bwd_wave(p->d, dtype, a, wave_grid(p, ps), st);
 }
 
 // Waves of a one-wave DTW sweep: the caller's, or ps.waves to a SIMD (four to
@@ -934,7 +949,7 @@ wts_status wts_softdtw_backward(const wts_plan* p, const double* bary, const voi
   const Layout l = layout(p, WTS_OP_SOFT_BWD);
   const PairSet& ps = p->soft;
   void* ck = const_cast<void*>(ckpt);
-  HIP_TRY(wts::launch_zero(at<int>(ws, l.queue), 2, st));
+  HIP_TRY(wts::launch_zero(at<int>(ws, l.queue), wts::kQueueWords, st));
   HIP_TRY(wts::launch_zero(at<int>(ws, l.progress), 3 * (int64_t)ps.n_flags, st));
   wts::SoftArgs a{};
   a.n_flags = ps.n_flags;
@@ -1005,7 +1020,7 @@ wts_status wts_softdtw_grad_cycles(const wts_plan* p, const double* bary, const 
   a.rows_packed = 1;
   a.items = ps.d_sweep_items;
   if ((rc = run_soft_fwd(p, ps, WTS_OP_SOFT_GRAD_C, WTS_F64, a, st)) != WTS_OK) return rc;
-  HIP_TRY(wts::launch_zero(a.queue, 2, st));
+  HIP_TRY(wts::launch_zero(a.queue, wts::kQueueWords, st));
   HIP_TRY(wts::launch_zero(a.progress, 3 * (int64_t)ps.n_flags, st));
   a.items = ps.d_items_rev;
   a.n_flags = ps.n_flags;

@@ -110,11 +110,18 @@ struct FwdArgs {
   int per_cu;            // one-wave sweeps, host only: workgroups a compute unit may hold (0: any)
 };
 
+// Words of the Soft-DTW backward's queue (zeroed before the launch): [0] counts
+// the items popped; the others, in a cache line of their own, serve a batch that
+// workgroups may hand over to waves: live tiles of the strips finished, the same
+// at the last look, the first item handed over plus one (0: none), and the
+// count of items popped from there.
+constexpr int kQueueWords = 64, kLiveTiles = 32, kLiveBefore = 33, kHandOver = 34, kHandQueue = 48;
+
 struct SoftArgs {
   const PairDesc* pairs;
   const int2* items;     // (pair, strip); strips descending within a pair for the backward
   int n_items;
-  int* queue;
+  int* queue;            // item counter (the backward: kQueueWords words)
   int* status;
   int* progress;         // per strip: columns published; the backward: three words a strip (BwdWords)
   int n_flags;           // strips of the pair set
@@ -134,6 +141,7 @@ struct SoftArgs {
   int rows_packed;       // 0: gsum/hsum rows at out * L + i; 1: at x_off + i (X rows packed)
   const int* skip;       // non-zero flag: the call's inputs failed validation, do nothing (or null)
   int zero_skip;         // backward: 1 = tiles whose e is exactly zero are not swept
+  int wave_tiles;        // backward by workgroups: live tiles a strip from which waves take over (0: never)
   unsigned long long* tiles;   // backward: += tiles swept, tiles of the strips' ranges (or null)
 };
 

@@ -74,7 +74,7 @@ hipError_t launch_medoid(const double* pair_dist, const int2* pair_ab, int n_pai
 hipError_t launch_soft_fwd(int d, int ydtype, const SoftArgs& a, int grid, hipStream_t st);
 hipError_t launch_soft_team(int d, int ydtype, const SoftArgs& a, int groups, hipStream_t st);
 hipError_t launch_soft_bwd(int d, int ydtype, const SoftArgs& a, int groups, hipStream_t st);
-hipError_t launch_soft_bwd_dense(int d, int ydtype, const SoftArgs& a, int grid, hipStream_t st);
+hipError_t launch_soft_bwd_wave(int d, int ydtype, const SoftArgs& a, int grid, hipStream_t st);
 hipError_t launch_soft_rows_scale(const double* g, const int64_t* off, int n, int64_t rows, int d,
                                   const double* w, double* out, hipStream_t st);
 hipError_t launch_soft_reduce(const double* gsum, const double* hsum, const double* w, int n,

@@ -3,6 +3,7 @@
 #pragma once
 
 #include <algorithm>
+#include <cmath>
 #include <cstddef>
 #include <cstdint>
 
@@ -51,6 +52,33 @@ inline bool team_pays(int rho, int64_t items, int cus, bool fp32) {
 // and at d = 6 2.27 / 2.23, 200 x 8k (12,600) 12.4 / 12.9 and at d = 6 16.3 /
 // 14.6.
 inline bool soft_team_pays(int64_t items, int cus) { return items <= 24 * (int64_t)cus; }
+
+// The Soft-DTW backward: a workgroup a strip (wts_soft_bwd.hip) or one wave a
+// strip (wts_soft_wave.hip).  A workgroup follows the strip below three to four
+// times as closely, and the chain of a pair's strips bounds batches of few
+// pairs or few live tiles (tiles with a non-zero e); one wave takes half the
+// time a tile once the tiles fill the compute units.  Measured on 256 compute
+// units, S strips a pair, n pairs, w live tiles a strip, in us:
+//   workgroup  n S (w + 8) (4.7 + 0.23 d) / 1000, at least 12.5 S + 1.3 w
+//   wave       S (72 + 3 d) + n S w (1.5 + 0.1 d) / 1000
+// The result is the w from which the wave is faster: 31 at 512 pairs, 165 at
+// 128, 10 at 1000.  w is 12 to 20 for a narrow E (a strip is 128 rows and
+// 63 steps of skew) and grows with gamma, up to 20 (cycles of 300), 48 (2k) or
+// 160 (20k) where every step is as likely: 1000 x 2k (d = 3) at 17 / 48 live tiles
+// 1.94 / 4.40 ms by workgroups, 1.71 / 2.59 by waves; 512 x 2k 1.02 / 2.26
+// against 1.52 / 1.96; 128 x 20k (d = 6) at 24 / 157 4.6 / 19.6 against 15.4 / 19.0.
+inline int bwd_wave_tiles(int64_t items, int strips, int cus, int d) {
+  const double n = (double)items / std::max(1, strips) * 256.0 / cus;
+  const double a = 4.7 + 0.23 * d, b = 1.5 + 0.1 * d, c = 1000.0 * (72.0 + 3.0 * d);
+  return (int)std::min(1e9, std::max(0.0, (c / std::max(n, 1e-3) - 8.0 * a) / (a - b)));
+}
+
+// Live tiles a strip can have, about, of a pair of that many rows and columns: its
+// 128 rows' columns and the spread where every step is as likely (20 at 300 x
+// 300, 48 at 2k x 2k, 160 at 20k x 20k).
+inline double bwd_live_most(double rows, double cols) {
+  return 8.0 * cols / std::max(1.0, rows) + std::sqrt(cols);
+}
 
 // Rows per lane of the barycenter sweeps when the caller leaves it open.
 // Batches of few strips take 2 and are swept by teams (in float32 above four

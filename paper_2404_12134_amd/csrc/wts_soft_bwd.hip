@@ -1,5 +1,6 @@
-// wts_soft_bwd.hip -- the Soft-DTW backward sweep (wts_soft.h describes it).
-#include "wts_soft.h"
+// wts_soft_bwd.hip -- the Soft-DTW backward sweep (wts_soft.h describes it), a
+// workgroup to a strip.
+#include "wts_soft_link.h"
 
 namespace wts {
 
@@ -29,17 +30,24 @@ constexpr int kBwdBufs = kBwdReplay + 1;      // tiles whose weights are in LDS 
 constexpr int kBwdSteps = kTile / kBwdReplay; // steps a replay wave takes a phase
 constexpr int kBwdRing = 256;                 // Y columns in LDS: seven tiles and the lanes' skew
 
-// A strip's words for the strip above (zeroed before the launch): columns
-// published, counted from the right; the tile of its first non-zero push, plus
-// one (-1: all its pushes are zero); the first column of its last published
-// tile.  Pushes outside [end, 16 start + 15] are zero and are not written, so
-// a strip waits on one word for the place where its input begins, however
-// many zero tiles lie to the right of it.
-struct BwdWords {
-  int* prog;
-  int* start;
-  int* end;
-};
+// Live tiles above wave_tiles, over all strips left, from which the rest of the
+// queue is handed to the waves: what the change itself takes, 0.1 to 0.15 ms.
+constexpr int kBwdHandOver = 50000;
+constexpr int kBwdWindow = 256;   // strips between two looks at the live tiles
+
+// The workgroup that popped item `it`, every window of strips, compares the live
+// tiles of the strips finished since the last look with wave_tiles (one thread;
+// each strip costs one atomic that nobody waits for).  To hand over, it moves
+// the item counter past the end, so that no workgroup pops any more, and leaves
+// the first item that was not popped for the waves.
+__device__ __forceinline__ void watch_width(const SoftArgs& a, int it) {
+  const int now = ld_dev(a.queue + kLiveTiles), before = ld_dev(a.queue + kLiveBefore);
+  st_dev(a.queue + kLiveBefore, now);
+  const int64_t over = (int64_t)(unsigned)(now - before) - (int64_t)kBwdWindow * a.wave_tiles;
+  if (over * (a.n_items - it) <= (int64_t)kBwdWindow * kBwdHandOver) return;
+  const int left = atomicAdd(a.queue, a.n_items);
+  if (left < a.n_items) st_dev(a.queue + kHandOver, left + 1);
+}
 
 template <typename TY, int D, int RHO, bool BAND>
 __global__ __launch_bounds__(kWave * kBwdWaves) void soft_bwd_kernel(SoftArgs a) {
@@ -65,7 +73,11 @@ __global__ __launch_bounds__(kWave * kBwdWaves) void soft_bwd_kernel(SoftArgs a)
   if (skipped(a.skip)) return;   // every workgroup: no strip waits for another
 
   for (;;) {
-    if (threadIdx.x == 0) s_item = atomicAdd(a.queue, 1);
+    if (threadIdx.x == 0) {
+      const int it = atomicAdd(a.queue, 1);
+      s_item = it;
+      if (a.wave_tiles > 0 && it > 0 && it % kBwdWindow == 0 && it < a.n_items) watch_width(a, it);
+    }
     __syncthreads();
     const int item = uni(s_item);
     if (item >= a.n_items) break;
@@ -135,17 +147,7 @@ __global__ __launch_bounds__(kWave * kBwdWaves) void soft_bwd_kernel(SoftArgs a)
     if (wv == 0) {
       // ---- push sweep, search and exchange
       const int bsl = lane == 0 ? 0 : kTile + lane;
-      const BwdWords below{a.progress + pd.flag_base + s + 1,
-                           a.progress + a.n_flags + pd.flag_base + s + 1,
-                           a.progress + 2 * a.n_flags + pd.flag_base + s + 1};
-      const BwdWords self{a.progress + pd.flag_base + s, a.progress + a.n_flags + pd.flag_base + s,
-                          a.progress + 2 * a.n_flags + pd.flag_base + s};
-      // rolling push rows: the strip below wrote them for us, we overwrite them
-      // for the strip above after reading
-      float* pu_row = a.push_up + pd.bnd_base;
-      float* pd_row = a.push_dg + pd.bnd_base;
-      const __amdgpu_buffer_rsrc_t pu_io = rsrc(pu_row, N * 4);
-      const __amdgpu_buffer_rsrc_t pd_io = rsrc(pd_row, N * 4);
+      BwdLink link(a, pd, s, g_lo, 4, 0);
       // the cell that closes the path, (M-1, N-1), receives e = 1: it is
       // pending as a left push into that cell before the sweep starts (lane
       // k_last computes no cell of its rows to the right of column N-1)
@@ -160,13 +162,6 @@ __global__ __launch_bounds__(kWave * kBwdWaves) void soft_bwd_kernel(SoftArgs a)
       }
       float up0 = 0.0f, dg0 = 0.0f;             // this lane's row-0 pushes, sent up next step
       float recv_dg = 0.0f;                     // diagonal push received last step
-      bool gave_up = false;                     // wave-uniform
-      int seen_below = 0;                       // last progress read from the strip below (uniform)
-      int in_hi = -1, in_lo = 0;                // columns of its pushes that may be non-zero
-      bool in_known = !has_below;               // in_hi is known; without a strip below, no input
-      bool in_done = false;                     // ... and in_lo is
-      bool started = false;                     // this strip's start word is out
-      int g_pub = 0;                            // last tile whose pushes were stored
       int n_swept = 0;
       // any push still travelling inside the strip (wave-uniform)
       auto pending = [&]() {
@@ -175,110 +170,13 @@ __global__ __launch_bounds__(kWave * kBwdWaves) void soft_bwd_kernel(SoftArgs a)
         for (int r = 0; r < RHO; ++r) p = p || pl[r] != 0.0f || pdg[r] != 0.0f;
         return __builtin_amdgcn_ballot_w64(p) != 0;
       };
-      // waits until *word satisfies ok, and returns it (uniform); 0 after a timeout
-      auto wait_word = [&](const int* word, int limit, auto ok) {
-        int got = 0, quit = 0;
-        if (lane == 0) {
-          int polls = 0;
-          got = ld_dev(word);
-          while (!ok(got)) {
-            if (polls > 4) poll_backoff(polls, 0);
-            if (++polls > limit) {
-              atomicOr(a.status, kStatusSpinTimeout);
-              quit = 1;
-              break;
-            }
-            got = ld_dev(word);
-          }
-        }
-        gave_up = __builtin_amdgcn_readfirstlane(quit) != 0;
-        const int r = __builtin_amdgcn_readfirstlane(got);
-        __atomic_signal_fence(__ATOMIC_SEQ_CST);
-        return r;
-      };
-      // the place where the input begins.  The strips below may sweep or pass over
-      // every tile of the pair before they push anything up (their tiles until
-      // then cover each column once, and five more a strip), a microsecond or two
-      // a tile, about a poll: two seconds for 2^24 columns.
-      auto learn_start = [&]() {
-        if (in_known || gave_up) return;
-        const int w = wait_word(below.start, kSpinLimit + 32 * (G + 16 * pd.S), [](int v) { return v != 0; });
-        in_known = true;
-        in_hi = w > 0 ? min(16 * (w - 1) + kTile - 1, N - 1) : -1;
-        if (w <= 0) { in_done = true; seen_below = N; }   // no input at all
-      };
-      auto learn_end = [&]() {
-        if (in_done || seen_below < N) return;
-        in_done = true;
-        int e = 0;
-        if (lane == 0) e = ld_dev(below.end);
-        in_lo = __builtin_amdgcn_readfirstlane(e);
-      };
-      // waits until the strip below has published every column >= jlo
-      auto wait_below = [&](int jlo) {
-        const int need = N - max(0, jlo);
-        if (need > seen_below && !gave_up)
-          seen_below = wait_word(below.prog, kSpinLimit, [&](int v) { return v >= need; });
-        learn_end();
-      };
-      // the pushes into columns [c, c + 64) of the bottom row, a column a lane
-      auto load_in = [&](int c, bool want, float& u, float& v) {
-        const int off = want && c >= max(in_lo, 0) && c <= in_hi ? c * 4 : kDrop;
-        u = ld_dev_f32(pu_io, off);
-        v = ld_dev_f32(pd_io, off);
-      };
-      // tiles gz .. g hold only zeros: published as such if earlier ones were
-      auto publish_zeros = [&](int gz, int g) {
-        if (!has_above || !started || gz > g) return;
-        for (int c = 16 * gz + lane; c < min(16 * g + kTile, N); c += kWave) {
-          st_dev(pu_io, c * 4, 0.0f);
-          st_dev(pd_io, c * 4, 0.0f);
-        }
-        mem_drain();
-        g_pub = gz;
-        if (lane == 0) st_dev(self.prog, N - min(N, 16 * gz));
-      };
-      // The next tile at or left of g that a push enters, with none travelling
-      // inside the strip; -1: there is none.  e reaches a cell only through the
-      // pushes of its successors, so every tile passed over has e = 0 in all its
-      // cells and pushes nothing on: skipping it leaves every bit of the sums
-      // as it is (a swept zero tile adds +0 and pushes 0 * w = 0).
-      auto search = [&](int g) {
-        if (!has_below) return -1;
-        learn_start();
-        if (gave_up) return -1;
-        g = min(g, (in_hi + kWave - 1) >> 4);
-        while (g >= g_lo) {
-          wait_below(16 * g - (kWave - 1));
-          if (gave_up || (in_done && 16 * g - (kWave - kTile) < in_lo) || in_hi < 0) return -1;
-          // tiles g .. ge: as far as the strip below has published, up to 16
-          int ge = max(g_lo, g - 15);
-          if (seen_below < N) ge = max(ge, (N - seen_below + (kWave - 1) + 15) >> 4);
-          const int jlo = 16 * ge - (kWave - 1);
-          const int cnt = 16 * (g - ge + 1);
-          int hit = -1;
-          float u[4], v[4];
-#pragma unroll
-          for (int q = 0; q < 4; ++q) load_in(jlo + lane + kWave * q, lane + kWave * q < cnt, u[q], v[q]);
-#pragma unroll
-          for (int q = 3; q >= 0; --q) {
-            const unsigned long long m = __builtin_amdgcn_ballot_w64(u[q] != 0.0f || v[q] != 0.0f);
-            if (hit < 0 && m != 0) hit = ge + ((kWave * q + 63 - __builtin_clzll(m)) >> 4);
-          }
-          publish_zeros(hit >= 0 ? hit + 1 : ge, g);
-          if (hit >= 0) return hit;
-          g = ge - 1;
-        }
-        return -1;
-      };
-
       int g = g_hi;
       bool more = false;   // the next phase's input is in in_up, in_dg
       float in_up = 0.0f, in_dg = 0.0f;
       for (;;) {
         int g0 = g >= g_lo ? g : -1;
-        if (g0 >= 0 && a.zero_skip && !pending()) g0 = search(g);
-        else if (g0 >= 0) learn_start();
+        if (g0 >= 0 && a.zero_skip && !pending()) g0 = link.search(g);
+        else if (g0 >= 0) link.learn_start();
         more = false;
         if (lane == 0) ctl[2] = g0;
         team_barrier();
@@ -292,12 +190,12 @@ __global__ __launch_bounds__(kWave * kBwdWaves) void soft_bwd_kernel(SoftArgs a)
             const int tg = 16 * g;
             const int jl = tg - (kWave - 1) + lane;
             if (!more) {
-              if (has_below) wait_below(tg - (kWave - 1));
-              load_in(jl, lane < kTile, in_up, in_dg);
+              if (has_below) link.wait_below(tg - (kWave - 1));
+              link.load_in(jl, lane < kTile, in_up, in_dg);
             }
             int pv = 0;   // the strip below's progress, read while the tile is swept
-            const bool peek = has_below && !gave_up && seen_below < N - max(0, tg - 16 - (kWave - 1));
-            if (peek && lane == 0) pv = ld_dev(below.prog);
+            const bool peek = has_below && !link.gave_up && link.seen_below < N - max(0, tg - 16 - (kWave - 1));
+            if (peek && lane == 0) pv = ld_dev(link.below.prog);
             if (lane < kTile) bin[lane] = make_float2(in_up, in_dg);
             __atomic_signal_fence(__ATOMIC_SEQ_CST);
             __builtin_amdgcn_wave_barrier();
@@ -337,7 +235,8 @@ __global__ __launch_bounds__(kWave * kBwdWaves) void soft_bwd_kernel(SoftArgs a)
                     // pushes add up to e up to one rounding of each subtraction
                     // (unbiased, where weights that summed to 1 only to float32
                     // rounding would drain or add ~1e-8 of the mass at every
-                    // cell, systematically)
+                    // cell, systematically).  Written out here and in the one-wave
+                    // form: as a shared function it cost this form 2.5 %
                     const float pu_ = e * wu[r];
                     const float pl_ = e * wl[r];
                     const float dpush = (e - pu_) - pl_;
@@ -365,48 +264,25 @@ __global__ __launch_bounds__(kWave * kBwdWaves) void soft_bwd_kernel(SoftArgs a)
             __atomic_signal_fence(__ATOMIC_SEQ_CST);
             __builtin_amdgcn_wave_barrier();
             if (peek) {
-              seen_below = max(seen_below, __builtin_amdgcn_readfirstlane(pv));
-              learn_end();
+              link.seen_below = max(link.seen_below, __builtin_amdgcn_readfirstlane(pv));
+              link.learn_end();
             }
-            if (has_above) {
-              // the top row's pushes for columns tg .. tg+15 (two stores, issued
-              // by every lane, dropped past the row), then the announcement of
-              // the previous tile's columns: waiting until at most these two
-              // stores are outstanding completes every older one
-              const int j = tg + lane;
-              const bool w = lane < kTile && j < N;
+            {
               const float2 o = bout[lane & (kTile - 1)];
-              if (!started) {
-                const bool nz = __builtin_amdgcn_ballot_w64(w && (o.x != 0.0f || o.y != 0.0f)) != 0;
-                started = nz || !a.zero_skip;
-                if (started && lane == 0) st_dev(self.start, g + 1);
-              }
-              if (started) {
-                st_dev(pu_io, w ? j * 4 : kDrop, o.x);
-                st_dev(pd_io, w ? j * 4 : kDrop, o.y);
-                mem_wait_all_but_2();
-                g_pub = g;
-                if (lane == 0) st_dev(self.prog, N - min(N, tg + kTile));
-              }
+              link.publish(g, o.x, o.y);
             }
             stop = g == g_lo || (a.zero_skip && !pending());
             --g;
-            more = !stop && (!has_below || gave_up || seen_below >= N - max(0, 16 * g - (kWave - 1)));
-            if (more) load_in(16 * g - (kWave - 1) + lane, lane < kTile, in_up, in_dg);
+            more = !stop && (!has_below || link.gave_up || link.seen_below >= N - max(0, 16 * g - (kWave - 1)));
+            if (more) link.load_in(16 * g - (kWave - 1) + lane, lane < kTile, in_up, in_dg);
           }
           if (lane == 0) ctl[ph & 1] = stop ? 1 : 0;
           team_barrier();
           if (stop) break;
         }
       }
-      if (has_above) {   // the last tile's columns; every one left of them is zero
-        if (lane == 0) {
-          if (started) st_dev(self.end, 16 * g_pub);
-          else st_dev(self.start, -1);
-        }
-        mem_drain();
-        if (lane == 0) st_dev(self.prog, N);
-      }
+      if (a.wave_tiles > 0 && lane == 0) atomicAdd(a.queue + kLiveTiles, n_swept);
+      link.finish();
       if (a.tiles != nullptr && lane == 0) {
         atomicAdd(a.tiles, (unsigned long long)n_swept);
         atomicAdd(a.tiles + 1, (unsigned long long)(g_hi - g_lo + 1));
@@ -485,23 +361,9 @@ __global__ __launch_bounds__(kWave * kBwdWaves) void soft_bwd_kernel(SoftArgs a)
 #pragma unroll
                 for (int r = 0; r < RHO; ++r) {
                   const double lf = left[r];
-                  double rv;
-                  if constexpr (BAND) {
-                    // outside the band: cost +inf and weights (1, 0, 0), so the
-                    // cell receives and passes on exactly nothing
-                    const bool inb = __builtin_fabs(bd0 + (double)r * (double)(N - 1)) <= band_b;
-                    const SoftMin sm = softmin3_band(dg, up, lf, inb);
-                    rv = inb ? sq_cost<D>(xr[r], xx[r], y[u], yy[u]) + sm.v : INF;
-                    const float rs = __builtin_amdgcn_rcpf(inb ? sm.s : 1.0f);
-                    wu[r] = inb ? sm.eu * rs : 0.0f;
-                    wl[r] = inb ? sm.el * rs : 0.0f;
-                  } else {
-                    const SoftMin sm = softmin3(dg, up, lf);
-                    rv = sq_cost<D>(xr[r], xx[r], y[u], yy[u]) + sm.v;
-                    const float rs = __builtin_amdgcn_rcpf(sm.s);   // s >= 1: the minimum's term is 1
-                    wu[r] = sm.eu * rs;
-                    wl[r] = sm.el * rs;
-                  }
+                  const bool inb = !BAND || __builtin_fabs(bd0 + (double)r * (double)(N - 1)) <= band_b;
+                  const double rv = replay_cell<D, BAND>(dg, up, lf, xr[r], xx[r], y[u], yy[u], inb,
+                                                         wu[r], wl[r]);
                   dg = lf;
                   up = rv;
                   left[r] = rv;

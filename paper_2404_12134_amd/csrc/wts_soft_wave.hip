@@ -1,24 +1,24 @@
-// wts_soft_dense.hip -- the Soft-DTW backward with every tile swept (plan
-// option dense_e) for batches of many strips: one wave a strip.
+// wts_soft_wave.hip -- the Soft-DTW backward, one wave to a strip, for batches
+// whose tiles with a non-zero e keep the compute units busy (many pairs, a wide
+// E, or every tile swept: plan option dense_e).
 //
-// The backward of wts_soft_bwd.hip gives a strip a whole compute unit, because
-// the chain of a pair's strips bounds it when few tiles hold a non-zero e.  With
-// every tile swept and many strips the arithmetic bounds it, and one wave that
-// replays, pushes and sums its tiles in turn, two to a SIMD, spends fewer
-// instructions a tile: 128 cycles of 8k (d = 6) 16.9 ms against 24.5, 512 of
-// 800 1.16 against 1.54; up to eight strips a compute unit the other is faster
-// (64 of 4k 3.5 against 3.3, 32 of 2k 1.27 against 0.50).
-// The strips of a pair are chained from the bottom up by the columns each has
-// published (a word a strip); the operations of a cell, and so its bits, are
-// those of wts_soft_bwd.hip.
-#include "wts_soft.h"
+// The workgroup form (wts_soft_bwd.hip) gives a strip a whole compute unit,
+// because the chain of a pair's strips bounds batches of few pairs.  Where the
+// arithmetic bounds it, one wave that replays, pushes and sums its tiles in
+// turn, two or three to a SIMD, spends fewer instructions a tile and needs no
+// barriers: wts_rules.h (bwd_wave_tiles) has the times of both and the line
+// between them.  2000 cycles of 1000 (d = 3, narrow / wide E) 1.84 / 3.59 ms by
+// workgroups, 1.02 / 2.1 by waves; every tile swept (d = 6): 128 x 8k 24.5 / 16.9,
+// 512 x 800 1.54 / 1.16, 64 x 4k 3.3 / 3.5.
+// The operations of a cell, and so its bits, are those of the workgroup form.
+#include "wts_soft_link.h"
 
 namespace wts {
 
 namespace {
 
 template <typename TY, int D, int RHO, bool BAND>
-__global__ __launch_bounds__(kWave, 2) void soft_bwd_dense_kernel(SoftArgs a) {
+__global__ __launch_bounds__(kWave, D <= 3 && !BAND ? 3 : 2) void soft_bwd_wave_kernel(SoftArgs a) {
   constexpr int H = kWave * RHO;
   __shared__ double ys[D][kRing + 16];     // -2 y' of the columns (see sq_cost)
   __shared__ double yq[kRing + 16];        // |y'|^2
@@ -37,9 +37,17 @@ __global__ __launch_bounds__(kWave, 2) void soft_bwd_dense_kernel(SoftArgs a) {
   const double k = a.kscale;
   const double sk = __builtin_sqrt(k);   // x and y enter as sqrt(k) (x - mu), sqrt(k) (y - mu)
   if (skipped(a.skip)) return;   // every workgroup: no strip waits for another
+  // the whole queue, or what the workgroups handed over
+  int first = 0;
+  int* queue = a.queue;
+  if (a.wave_tiles > 0) {
+    first = uni(ld_dev(a.queue + kHandOver)) - 1;
+    if (first < 0) return;
+    queue = a.queue + kHandQueue;
+  }
 
   for (;;) {
-    if (lane == 0) s_item = atomicAdd(a.queue, 1);
+    if (lane == 0) s_item = first + atomicAdd(queue, 1);
     __syncthreads();
     const int item = __builtin_amdgcn_readfirstlane(s_item);   // uniform: scalar loads below
     __syncthreads();
@@ -63,9 +71,7 @@ __global__ __launch_bounds__(kWave, 2) void soft_bwd_dense_kernel(SoftArgs a) {
     // lanes) all lie outside the band of the strip's rows has e = 0 in every
     // cell (a cell outside the band gets nothing from its successors: their
     // weight towards a +inf cell is 0), so the sweep runs tiles g_lo .. g_hi
-    // only.  The strip above never reads pushes right of our tiles (the
-    // band's right edge moves right from row to row); the columns left of
-    // them are published as zeros at the end.
+    // only.
     int g_lo = 0, g_hi = G - 1;
     if (BAND) {
       int jlo_b, jhi_b;
@@ -76,12 +82,7 @@ __global__ __launch_bounds__(kWave, 2) void soft_bwd_dense_kernel(SoftArgs a) {
     const double* row_fwd = a.rows + pd.aux_base + (int64_t)(s - 1) * N;
     const double* st = a.states + pd.state_base + (int64_t)s * G * (RHO + 1) * kWave;
     const __amdgpu_buffer_rsrc_t rf_in = rsrc(row_fwd, has_above ? N * 8 : 0);
-    // rolling push rows: the strip below wrote them for us, we overwrite them
-    // for the strip above after reading
-    float* pu_row = a.push_up + pd.bnd_base;
-    float* pd_row = a.push_dg + pd.bnd_base;
-    int* prog_below = a.progress + pd.flag_base + s + 1;
-    int* prog_self = a.progress + pd.flag_base + s;
+    BwdLink link(a, pd, s, g_lo, 0, a.relaxed_wait);
     // the cell that closes the path, (M-1, N-1), receives e = 1: it is
     // pending as a left push into that cell before the sweep starts (lane
     // k_last computes no cell of its rows to the right of column N-1)
@@ -111,12 +112,13 @@ __global__ __launch_bounds__(kWave, 2) void soft_bwd_dense_kernel(SoftArgs a) {
     }
     float up0 = 0.0f, dg0 = 0.0f;             // this lane's row-0 pushes, sent up next step
     float recv_dg = 0.0f;                     // diagonal push received last step
-    bool gave_up = false;                     // wave-uniform
-    int seen_below = 0;                       // last progress read from the strip below (uniform)
-    const __amdgpu_buffer_rsrc_t pu_out = rsrc(pu_row, N * 4);
-    const __amdgpu_buffer_rsrc_t pd_out = rsrc(pd_row, N * 4);
-    const __amdgpu_buffer_rsrc_t pu_in = rsrc(pu_row, has_below ? N * 4 : 0);
-    const __amdgpu_buffer_rsrc_t pd_in = rsrc(pd_row, has_below ? N * 4 : 0);
+    // any push still travelling inside the strip (wave-uniform)
+    auto pending = [&]() {
+      bool p = up0 != 0.0f || dg0 != 0.0f || recv_dg != 0.0f;
+#pragma unroll
+      for (int r = 0; r < RHO; ++r) p = p || pl[r] != 0.0f || pdg[r] != 0.0f;
+      return __builtin_amdgcn_ballot_w64(p) != 0;
+    };
     // a tile's replay inputs: the forward's sweep state at its first step and
     // (lanes 0..15) the strip above's bottom row at its 16 columns (the top
     // strip reads an empty buffer and uses +inf; columns past N are never used)
@@ -142,34 +144,23 @@ __global__ __launch_bounds__(kWave, 2) void soft_bwd_dense_kernel(SoftArgs a) {
         ring_col<D>(ys, yq, j & (kRing - 1), yc);
       }
     };
-    // waits until the strip below has published every column >= jlo
-    auto wait_below = [&](int jlo) {
-      const int need = N - max(0, jlo);
-      if (need > seen_below && !gave_up) {
-        int got = 0, quit = 0;
-        if (lane == 0) {
-          int polls = 0;
-          got = ld_dev(prog_below);
-          while (got < need) {
-            poll_backoff(polls, a.relaxed_wait);
-            if (++polls > kSpinLimit) {
-              atomicOr(a.status, kStatusSpinTimeout);
-              quit = 1;
-              break;
-            }
-            got = ld_dev(prog_below);
-          }
-        }
-        seen_below = __builtin_amdgcn_readfirstlane(got);
-        gave_up = __builtin_amdgcn_readfirstlane(quit) != 0;
-      }
-      __atomic_signal_fence(__ATOMIC_SEQ_CST);
-    };
-
-    load_tile_inputs(g_hi);
-    fill_ring(g_hi);
-
+    int n_swept = 0;
+    bool ready = false;   // tile g's replay inputs and Y columns are here or in flight
     for (int g = g_hi; g >= g_lo; --g) {
+      if (a.zero_skip && !pending()) {
+        const int next = link.search(g);
+        ready = ready && next == g;
+        g = next;
+        if (g < 0) break;
+      } else {
+        link.learn_start();
+      }
+      if (!ready) {
+        load_tile_inputs(g);
+        fill_ring(g);
+        ready = true;
+      }
+      ++n_swept;
       const int tg = 16 * g;
       const int yb = (tg - lane) & (kRing - 1);   // ring slot of step 0's column
       // next tile's 16 new Y columns, stored after this tile
@@ -189,17 +180,12 @@ __global__ __launch_bounds__(kWave, 2) void soft_bwd_dense_kernel(SoftArgs a) {
       // tg-63 ..  The strip below usually runs far ahead: one read of its
       // counter covers many tiles, and only a counter short of what this
       // tile needs is read again.
-      if (has_below) wait_below(tg - (kWave - 1));
+      if (has_below) link.wait_below(tg - (kWave - 1));
       // the pushes are only needed by the backward half: loaded now (one
       // unconditional load each, zero outside the row or without a strip
       // below) and written to LDS after the replay
       float in_up, in_dg;
-      {
-        const int j = tg - (kWave - 1) + lane;
-        const int off = lane < kTile && j >= 0 && j < N ? j * 4 : kDrop;
-        in_up = ld_dev_f32(pu_in, off);
-        in_dg = ld_dev_f32(pd_in, off);
-      }
+      link.load_in(tg - (kWave - 1) + lane, lane < kTile, in_up, in_dg);
       __syncthreads();
 
       // ---- replay the tile forward, keeping the soft-min weights
@@ -240,28 +226,11 @@ __global__ __launch_bounds__(kWave, 2) void soft_bwd_dense_kernel(SoftArgs a) {
 #pragma unroll
           for (int r = 0; r < RHO; ++r) {
             const double lf = left[r];
-            if constexpr (BAND) {
-              // outside the band: cost +inf and weights (1, 0, 0), so the cell
-              // receives and passes on exactly nothing
-              const bool inb = __builtin_fabs(bd0 + (double)r * (double)(N - 1)) <= band_b;
-              const SoftMin sm = softmin3_band(dg, up, lf, inb);
-              const double rv = inb ? sq_cost<D>(xr[r], xx[r], y, yy) + sm.v : INF;
-              const float rs = __builtin_amdgcn_rcpf(inb ? sm.s : 1.0f);
-              wu[u][r] = inb ? sm.eu * rs : 0.0f;
-              wl[u][r] = inb ? sm.el * rs : 0.0f;
-              dg = lf;
-              up = rv;
-              left[r] = rv;
-            } else {
-              const SoftMin sm = softmin3(dg, up, lf);
-              const double rv = sq_cost<D>(xr[r], xx[r], y, yy) + sm.v;
-              const float rs = __builtin_amdgcn_rcpf(sm.s);   // s >= 1: the minimum's term is 1
-              wu[u][r] = sm.eu * rs;
-              wl[u][r] = sm.el * rs;
-              dg = lf;
-              up = rv;
-              left[r] = rv;
-            }
+            const bool inb = !BAND || __builtin_fabs(bd0 + (double)r * (double)(N - 1)) <= band_b;
+            const double rv = replay_cell<D, BAND>(dg, up, lf, xr[r], xx[r], y, yy, inb, wu[u][r], wl[u][r]);
+            dg = lf;
+            up = rv;
+            left[r] = rv;
           }
           bot = left[RHO - 1];
         }
@@ -303,17 +272,12 @@ __global__ __launch_bounds__(kWave, 2) void soft_bwd_dense_kernel(SoftArgs a) {
 #pragma unroll
           for (int c = 0; c < D; ++c) y[c] = ys[c][yb + u];
           float below_up = recv_up;          // push up from (i+1, j)
-          float new_pdg[RHO];
+          float new_pdg[RHO], er[RHO];
 #pragma unroll
           for (int r = RHO - 1; r >= 0; --r) {
             const float din = (r == RHO - 1) ? recv_dg : pdg[r];
             const float e = (below_up + pl[r]) + din;
-            // e in [0, 1] is carried in float32; the row sums take it in
-            // float64.  Split e over the three predecessors: up and left by
-            // their weights, the diagonal takes the rest, so the three pushes
-            // add up to e up to one rounding of each subtraction (unbiased,
-            // where weights that summed to 1 only to float32 rounding would
-            // drain or add ~1e-8 of the mass at every cell, systematically)
+            // (the split over the predecessors: see wts_soft_bwd.hip)
             const float pu_ = e * wu[u][r];
             const float pl_ = e * wl[u][r];
             const float dpush = (e - pu_) - pl_;
@@ -321,14 +285,18 @@ __global__ __launch_bounds__(kWave, 2) void soft_bwd_dense_kernel(SoftArgs a) {
             pl[r] = pl_;
             if (r > 0) new_pdg[r - 1] = dpush;
             else dg0 = dpush;
-            const double e64 = e;
-            acc_e[r] += e64;
-#pragma unroll
-            for (int c = 0; c < D; ++c) acc_ey[r][c] = __builtin_fma(e64, y[c], acc_ey[r][c]);
+            er[r] = e;
           }
           up0 = below_up;
 #pragma unroll
           for (int r = 0; r + 1 < RHO; ++r) pdg[r] = new_pdg[r];
+#pragma unroll
+          for (int r = RHO - 1; r >= 0; --r) {
+            const double e64 = er[r];
+            acc_e[r] += e64;
+#pragma unroll
+            for (int c = 0; c < D; ++c) acc_ey[r][c] = __builtin_fma(e64, y[c], acc_ey[r][c]);
+          }
         }
         // lane 0's pushes into slot u (a column past N holds a stale value,
         // never published), the other lanes' into scratch slots: no branch
@@ -337,18 +305,7 @@ __global__ __launch_bounds__(kWave, 2) void soft_bwd_dense_kernel(SoftArgs a) {
         recv_dg = recv_dg_next;
       }
       __syncthreads();
-      if (has_above) {
-        // publish the top row's pushes for columns tg .. tg+15 (two stores,
-        // issued by every lane, dropped past the row), then announce the
-        // previous tile's columns: waiting until at most these two stores are
-        // outstanding completes every older store without waiting for them
-        const int j = tg + lane;
-        const bool w = lane < kTile && j < N;
-        st_dev(pu_out, w ? j * 4 : kDrop, bout_up[lane & (kTile - 1)]);
-        st_dev(pd_out, w ? j * 4 : kDrop, bout_dg[lane & (kTile - 1)]);
-        mem_wait_all_but_2();
-        if (lane == 0) st_dev(prog_self, N - min(N, tg + 16));
-      }
+      link.publish(g, bout_up[lane & (kTile - 1)], bout_dg[lane & (kTile - 1)]);
       if (g > 0 && lane < 16) {
         const bool in = jn >= 0 && jn < N;
         double yc[D];
@@ -358,39 +315,9 @@ __global__ __launch_bounds__(kWave, 2) void soft_bwd_dense_kernel(SoftArgs a) {
       }
       __syncthreads();
     }
-    if (has_above) {   // the last tile's columns
-      if (BAND && g_lo > 0) {
-        // columns 0 .. 16 g_lo - 1 of the top row push nothing: zeros, written
-        // once the strip below has finished with the shared row (it writes
-        // its own pushes for us there)
-        if (has_below && !gave_up) {
-          int got = 0, quit = 0;
-          if (lane == 0) {
-            int polls = 0;
-            got = ld_dev(prog_below);
-            while (got < N) {
-              poll_backoff(polls, a.relaxed_wait);
-              if (++polls > kSpinLimit) {
-                atomicOr(a.status, kStatusSpinTimeout);
-                quit = 1;
-                break;
-              }
-              got = ld_dev(prog_below);
-            }
-          }
-          gave_up = __builtin_amdgcn_readfirstlane(quit) != 0;
-        }
-        __atomic_signal_fence(__ATOMIC_SEQ_CST);
-        for (int j = lane; j < 16 * g_lo; j += kWave) {
-          st_dev(pu_out, j * 4, 0.0f);
-          st_dev(pd_out, j * 4, 0.0f);
-        }
-      }
-      mem_drain();
-      if (lane == 0) st_dev(prog_self, N);
-    }
+    link.finish();
     if (a.tiles != nullptr && lane == 0) {
-      atomicAdd(a.tiles, (unsigned long long)(g_hi - g_lo + 1));
+      atomicAdd(a.tiles, (unsigned long long)n_swept);
       atomicAdd(a.tiles + 1, (unsigned long long)(g_hi - g_lo + 1));
     }
     // per-row sums of this cycle: gradient 2 (b sum_j e - sum_j e y_j), which
@@ -413,17 +340,17 @@ __global__ __launch_bounds__(kWave, 2) void soft_bwd_dense_kernel(SoftArgs a) {
 }  // namespace
 
 template <typename TY, int D>
-static hipError_t launch_soft_dense_t(const SoftArgs& a, int grid, hipStream_t st) {
+static hipError_t launch_soft_wave_t(const SoftArgs& a, int grid, hipStream_t st) {
   if (a.band > 0.0)
-    hipLaunchKernelGGL((soft_bwd_dense_kernel<TY, D, kSoftRho, true>), dim3(grid), dim3(kWave), 0, st, a);
+    hipLaunchKernelGGL((soft_bwd_wave_kernel<TY, D, kSoftRho, true>), dim3(grid), dim3(kWave), 0, st, a);
   else
-    hipLaunchKernelGGL((soft_bwd_dense_kernel<TY, D, kSoftRho, false>), dim3(grid), dim3(kWave), 0, st, a);
+    hipLaunchKernelGGL((soft_bwd_wave_kernel<TY, D, kSoftRho, false>), dim3(grid), dim3(kWave), 0, st, a);
   return hipGetLastError();
 }
 
-hipError_t launch_soft_bwd_dense(int d, int ydtype, const SoftArgs& a, int grid, hipStream_t st) {
-#define CALLS(D) (ydtype == 0 ? launch_soft_dense_t<float, D>(a, grid, st) \
-                              : launch_soft_dense_t<double, D>(a, grid, st))
+hipError_t launch_soft_bwd_wave(int d, int ydtype, const SoftArgs& a, int grid, hipStream_t st) {
+#define CALLS(D) (ydtype == 0 ? launch_soft_wave_t<float, D>(a, grid, st) \
+                              : launch_soft_wave_t<double, D>(a, grid, st))
   WTS_SOFT_D_SWITCH(d, CALLS)
 #undef CALLS
 }
