@@ -80,27 +80,33 @@ __global__ __launch_bounds__(kWave) void walk_kernel(WalkArgs a) {
 // The DBA update from the row runs: per cycle and row the sum of the cycle's
 // samples over the run [lo, hi] in descending column order, folded over the
 // cycles in ascending order with their weights, and the mean.  A workgroup
-// takes kFoldRows rows and kFoldCycles cycles at a time: each thread sums one
+// takes ROWS rows and 256 / ROWS cycles at a time: each thread sums one
 // (cycle, row) run, then one thread per (row, channel) folds the sums from
 // LDS in order, so no per-cycle sums go through memory.  Bound by the launch and
 // one trip to memory on small batches (4 us of the 62 of a DBA iteration on 8
-// cycles of 230).
-constexpr int kFoldRows = 16, kFoldCycles = 16;
-template <typename TY, int D>
-__global__ __launch_bounds__(kFoldRows * kFoldCycles)
+// cycles of 230), else by the trips to memory of a workgroup's cycles.
+// ROWS: 4, and 1 up to 512 rows (two workgroups a compute unit), where the
+// cycles of a row are the more to share.  DBA iteration, us, at 16 / 4 / 1 rows: 1000 cycles
+// of 1000 (L = 16) 783 / 381 / 272, 512 of 20k (L = 500) 4723 / 4426 / 4371, 300 of
+// 1000 (L = 1000) 465 / 447 / 457, 512 of 8k (L = 8000, d = 6) 21.19 / 21.12 / 21.42 ms.
+constexpr int kFoldThreads = 256;
+constexpr int64_t kFoldFewRows = 512;
+template <typename TY, int D, int ROWS>
+__global__ __launch_bounds__(kFoldThreads)
 void run_fold_kernel(const int2* __restrict__ runs, const int64_t* __restrict__ off, const void* y,
                      const double* __restrict__ w, int n, int64_t L, double* __restrict__ bout,
                      int64_t* __restrict__ counts, const int* skip) {
-  __shared__ double ps[kFoldCycles][D][kFoldRows];
-  __shared__ int pc[kFoldCycles][kFoldRows];
+  constexpr int kCycles = kFoldThreads / ROWS;
+  __shared__ double ps[kCycles][D][ROWS];
+  __shared__ int pc[kCycles][ROWS];
   if (skipped(skip)) return;
   const TY* __restrict__ Y = static_cast<const TY*>(y);
-  const int q = threadIdx.x / kFoldRows, row = threadIdx.x % kFoldRows;
-  const int64_t l = blockIdx.x * (int64_t)kFoldRows + row;
-  const int fc = threadIdx.x / kFoldRows;   // the channel this thread folds (fc < D)
+  const int q = threadIdx.x / ROWS, row = threadIdx.x % ROWS;
+  const int64_t l = blockIdx.x * (int64_t)ROWS + row;
+  const int fc = threadIdx.x / ROWS;   // the channel this thread folds (fc < D)
   double S = 0.0, C = 0.0;
   int64_t K = 0;
-  for (int p0 = 0; p0 < n; p0 += kFoldCycles) {
+  for (int p0 = 0; p0 < n; p0 += kCycles) {
     const int p = p0 + q;
     if (p < n && l < L) {
       const int2 rn = runs[(int64_t)p * L + l];
@@ -108,7 +114,19 @@ void run_fold_kernel(const int2* __restrict__ runs, const int64_t* __restrict__ 
       double acc[D];
 #pragma unroll
       for (int c = 0; c < D; ++c) acc[c] = 0.0;
-      for (int jj = rn.y; jj >= rn.x; --jj) {
+      int jj = rn.y;
+      for (; jj >= rn.x + 7; jj -= 8) {   // long runs: eight samples in flight
+        TY v[8][D];
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+#pragma unroll
+          for (int c = 0; c < D; ++c) v[u][c] = Y[(base + jj - u) * D + c];
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+#pragma unroll
+          for (int c = 0; c < D; ++c) acc[c] = acc[c] + static_cast<double>(v[u][c]);
+      }
+      for (; jj >= rn.x; --jj) {
 #pragma unroll
         for (int c = 0; c < D; ++c) acc[c] = acc[c] + static_cast<double>(Y[(base + jj) * D + c]);
       }
@@ -118,7 +136,8 @@ void run_fold_kernel(const int2* __restrict__ runs, const int64_t* __restrict__ 
     }
     __syncthreads();
     if (fc < D && l < L) {
-      const int m = min(kFoldCycles, n - p0);
+      const int m = min(kCycles, n - p0);
+#pragma unroll 4
       for (int e = 0; e < m; ++e) {
         const double wp = w ? w[p0 + e] : 1.0;
         const int k = pc[e][row];
@@ -301,8 +320,13 @@ template <typename TY, int D>
 static hipError_t launch_run_fold_t(const int2* runs, const int64_t* off, const void* y,
                                     const double* w, int n, int64_t L, double* bout,
                                     int64_t* counts, const int* skip, hipStream_t st) {
-  hipLaunchKernelGGL((run_fold_kernel<TY, D>), dim3((unsigned)((L + kFoldRows - 1) / kFoldRows)),
-                     dim3(kFoldRows * kFoldCycles), 0, st, runs, off, y, w, n, L, bout, counts, skip);
+  auto go = [&](auto rows) {
+    constexpr int R = decltype(rows)::value;
+    hipLaunchKernelGGL((run_fold_kernel<TY, D, R>), dim3((unsigned)((L + R - 1) / R)),
+                       dim3(kFoldThreads), 0, st, runs, off, y, w, n, L, bout, counts, skip);
+  };
+  if (L <= kFoldFewRows) go(std::integral_constant<int, 1>{});
+  else go(std::integral_constant<int, 4>{});
   return hipGetLastError();
 }
 
