@@ -180,17 +180,19 @@ void dtw_fwd_kernel(FwdArgs a) {
     TC left[RHO];
     int lx[RHO];
     uint32_t accd[RHO], accu[RHO];   // code planes: diagonal chosen; up not above left
+    int tb = border_tag<MODE>(ib);   // (opaque: known as -ib, it cost the float32 sweep of d = 6 5 %)
+    if (MODE == MODE_DIST_LEN) __asm__("" : "+v"(tb));
 #pragma unroll
-    for (int r = 0; r < RHO; ++r) { left[r] = INF; lx[r] = border_tag<MODE>(ib + r); accd[r] = accu[r] = 0u; }
+    for (int r = 0; r < RHO; ++r) { left[r] = INF; lx[r] = MODE == MODE_DIST_LEN ? tb - r : 0; accd[r] = accu[r] = 0u; }
     TC upprev = (s == 0 && lane == 0) ? (TC)0 : INF;   // r(-1,-1) = 0 at the origin
     // Sub-DTW: running minimum of the last row (lowest column on ties)
     const bool last_strip = s + 1 == pd.S;
     const int rl_last = M - 1 - ib;
     TC sub_best = INF;
     int sub_end = 0, sub_start = 0;
-    int upprevx = border_tag<MODE>(ib - 1);
+    int upprevx = MODE == MODE_DIST_LEN ? tb + 1 : 0;
     TC bot = INF;
-    int botx = border_tag<MODE>(ib + RHO - 1);
+    int botx = lx[RHO - 1];
     bool gave_up = false;   // set once a wait times out: the strip never waits again
 
     // The strip above's bottom row, 16 columns at a time: lanes 0..15 hold the
