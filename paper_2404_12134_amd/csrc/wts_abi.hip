@@ -60,7 +60,8 @@ struct PairSet {
   int max_strips = 0;        // of a pair
   double live_most = 0.0;    // live tiles a strip can have, about
   int rho = 4;   // barycenter rows per lane of this set's sweeps
-  int waves = 1;             // one-wave sweeps: waves per SIMD
+  SweepLoad load;            // strips and steps of the sweeps
+  int waves[kSweepKinds] = {1, 1, 1, 1};   // one-wave sweeps: waves per SIMD, by kind
   bool team = false;         // swept by teams of four waves a strip
   bool walk_pairs = false;   // path recovery one pair at a time, from checkpoints (CKPT sweep)
 };
@@ -108,6 +109,7 @@ void build_set(PairSet& ps, std::vector<Job> jobs, int rho, bool soft) {
     for (int s = 0; s < d.S; ++s) ps.items.push_back(make_int2((int)p, s));
     ps.pairs.push_back(d);
     ps.max_rows = std::max<int64_t>(ps.max_rows, jb.M);
+    ps.load.add(jb.N, d.S);
     ps.tiles += (int64_t)d.S * d.WT;
     ps.max_strips = std::max(ps.max_strips, d.S);
     ps.live_most = std::max(ps.live_most, bwd_live_most(jb.M, jb.N));
@@ -149,35 +151,6 @@ struct Layout {
 constexpr int kMaxDevices = 64;
 std::mutex g_scratch_mu;
 void* g_scratch[kMaxDevices] = {};
-
-// Waves per SIMD of the one-wave sweeps.  A second wave on a SIMD raises its
-// throughput (a step of both takes 1.67 times a step of one in float64, 1.3
-// in float32) and slows the chain of every pair's strips by as much, and the
-// deeper the strips of a pair are resident, the longer they wait for each
-// other at the start (about 300 steps a strip).  In steps of one wave: the
-// longest pair's chain, or all strips over the SIMDs.  Measured, score sweep
-// of d = 3 at 1 / 2 / 3 waves: 20 cycles of 2.5k-40k samples (L = 20,000) 7.3
-// / 10.4 / 10.2 ms, 50 of 20k 13.0 / 14.0 / 14.0, 512 of 1k-20k (L = 10,000)
-// 20.7 / 17.2 / 18.3.  Three waves gain where the instruction mix is light:
-// value sweeps of few channels (medoid of 64 x 5k, d = 3: 16.6 / 16.2 ms at 2 /
-// 3) and float32 (512 cycles, d = 6: 17.7 / 17.1).
-int sweep_waves(const PairSet& ps, int cus, int d, bool fp32, bool values) {
-  const double simds = 4.0 * cus;
-  double work = 0.0, chain = 0.0, smax = 0.0;
-  for (const PairDesc& q : ps.pairs) {
-    const double steps = 16.0 * q.WT;
-    work += steps * q.S;
-    chain = std::max(chain, steps + 120.0 * q.S);
-    smax = std::max(smax, (double)q.S);
-  }
-  if (ps.n_items <= simds) return 1;
-  work /= simds;
-  auto depth = [&](int w) { return std::min(smax, w * simds / std::max(1, ps.n_pairs)); };
-  const double one = std::max(chain, work + 120.0 * depth(1));
-  const double two = (fp32 ? 1.3 : 1.67) * std::max(chain, work / 2 + 300.0 * depth(2));
-  if (one <= two) return 1;
-  return (values && d <= 4) || (fp32 && ps.n_items > 6 * simds) ? 3 : 2;
-}
 
 }  // namespace
 
@@ -287,31 +260,6 @@ Layout layout(const wts_plan* p, int op) {
 template <typename T>
 T* at(void* ws, size_t off) { return reinterpret_cast<T*>(static_cast<char*>(ws) + off); }
 
-// Path recovery.  Codes and entry tags for every cell (PATHT) cost the
-// one-wave sweep about 28 instructions a step of 4 rows (62 ns with one wave
-// to a SIMD, 36 ns with more) and let all strips be walked at once, in about
-// 0.1 ms.  From checkpoints (CKPT) the sweep is the value sweep, and each
-// pair's strips are swept again along its path and walked in turn, 23 us and
-// 2.4 us a channel a strip (above 256 pairs they share the compute units).
-// Measured per DBA iteration, codes / checkpoints: 512 cycles of 1k-20k
-// samples (L = 10,000, d = 6) 25.3 / 22.8 ms, 25 of 30k (d = 3) 18.1 / 15.5,
-// 25 of 30k (d = 8) 27.0 / 27.2, 64 of 4k (d = 3) 1.27 / 1.22.  A team's sweep
-// costs less a strip than its walk: codes.
-bool walk_pairs_pays(const PairSet& ps, int cus, int d) {
-  if (ps.team) return false;
-  double work = 0.0, chain = 0.0;
-  int smax = 0;
-  for (const PairDesc& q : ps.pairs) {
-    const double steps = 16.0 * q.WT;
-    work += steps * q.S;
-    chain = std::max(chain, steps + 120.0 * q.S);
-    smax = std::max(smax, q.S);
-  }
-  const double steps = std::max(chain, work / (4.0 * cus));
-  return steps * (ps.waves == 1 ? 62e-9 : 36e-9) * ps.rho / 4 >
-         smax * (23e-6 + 2.4e-6 * d) * std::max(1.0, ps.n_pairs / 256.0);
-}
-
 int default_grid(const wts_plan* p, const PairSet& ps) {   // Soft-DTW sweeps
   // 24 one-wave workgroups per CU; the sweeps' registers cap the resident
   // waves lower by themselves.
@@ -349,10 +297,10 @@ hipError_t run_soft_bwd(const wts_plan* p, const PairSet& ps, int dtype, wts::So
   return wts::launch_soft_bwd_wave(p->d, dtype, a, wave_grid(p, ps), st);
 }
 
-// Waves of a one-wave DTW sweep: the caller's, or ps.waves to a SIMD (four to
-// a workgroup, ps.waves workgroups to a compute unit).
-int dtw_grid(const wts_plan* p, const PairSet& ps) {
-  const int g = p->opts.grid > 0 ? p->opts.grid : 4 * p->cus * ps.waves;
+// Waves of a one-wave DTW sweep: the caller's, or that many to a SIMD (four to a
+// workgroup, as many workgroups to a compute unit).
+int dtw_grid(const wts_plan* p, const PairSet& ps, int waves) {
+  const int g = p->opts.grid > 0 ? p->opts.grid : 4 * p->cus * waves;
   return std::max(1, std::min(g, ps.n_items));
 }
 
@@ -463,7 +411,9 @@ wts_status run_sweep(const wts_plan* p, const PairSet& ps, int mode, bool euc, b
   a.out_aux = at<int>(ws, l.out_aux);
   a.out_end = mode == wts::MODE_SUB ? at<int>(ws, l.out_end) : nullptr;
   a.cost_kind = euc ? 1 : 0;
-  a.per_cu = p->opts.grid > 0 ? 0 : ps.waves;
+  const int waves = ps.waves[mode == wts::MODE_DIST ? kSweepValues : mode == wts::MODE_DIST_LEN ? kSweepScores
+                             : mode == wts::MODE_SUB ? kSweepSub : kSweepPaths];
+  a.per_cu = p->opts.grid > 0 ? 0 : waves;
   a.relaxed_wait = ps.n_items > 16 * p->cus ? 1 : 0;   // > 4 items per SIMD
   const int tk = timing_begin(p, x_is_cycle ? WTS_OP_MEDOID
                                  : mode == wts::MODE_CKPT || mode == wts::MODE_PATHT ? WTS_OP_DBA
@@ -474,7 +424,7 @@ wts_status run_sweep(const wts_plan* p, const PairSet& ps, int mode, bool euc, b
                              std::min(ps.n_items, 8 * p->cus), st));
   else
     HIP_TRY(wts::launch_fwd(p->d, ps.rho, mode, euc, x_is_cycle, p->dtype, fp32, a,
-                            dtw_grid(p, ps), st));
+                            dtw_grid(p, ps, waves), st));
   timing_end(p, tk, st);
   return WTS_OK;
 }
@@ -599,9 +549,11 @@ wts_status wts_plan_create(wts_plan** out, int device, int32_t n, int32_t d, int
     const int rho = o.rho ? o.rho : plan_rho(p->off.data(), n, L, p->cus, d, fp32, team);
     build_set(p->bary, jobs, rho, false);
     p->bary.team = team && team_pays(p->bary.rho, p->bary.n_items, p->cus, fp32);
-    p->bary.waves = sweep_waves(p->bary, p->cus, d, fp32, false);
+    for (int kind : {kSweepScores, kSweepSub, kSweepPaths})
+      p->bary.waves[kind] = sweep_waves(p->bary.load, kind, p->cus, d, rho, fp32);
     p->bary.walk_pairs = o.walk == WTS_WALK_PAIRS ||
-                         (o.walk == WTS_WALK_AUTO && walk_pairs_pays(p->bary, p->cus, d));
+                         (o.walk == WTS_WALK_AUTO && !p->bary.team &&
+                          walk_pairs_pays(p->bary.load, p->cus, d, rho, fp32));
     build_set(p->soft, jobs, wts::kSoftRho, true);
     std::vector<Job> tjobs;
     for (int k = 0; k < n; ++k)
@@ -629,7 +581,7 @@ wts_status wts_plan_create(wts_plan** out, int device, int32_t n, int32_t d, int
     build_set(p->med, jobs, p->rho, false);
     const bool fp32 = o.decision == WTS_DECISION_FP32;
     p->med.team = o.grid == 0 && team_pays(p->rho, p->med.n_items, p->cus, fp32);
-    p->med.waves = sweep_waves(p->med, p->cus, d, fp32, true);
+    p->med.waves[kSweepValues] = sweep_waves(p->med.load, kSweepValues, p->cus, d, p->rho, fp32);
     if (!ab.empty()) {
       hipError_t e;
       if ((e = hipMalloc(&p->d_med_ab, sizeof(int2) * ab.size())) != hipSuccess) return cleanup_fail(e, "hipMalloc");

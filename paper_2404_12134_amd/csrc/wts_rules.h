@@ -43,6 +43,81 @@ inline bool team_pays(int rho, int64_t items, int cus, bool fp32) {
   return rho == 4 && items <= (fp32 ? 4 : 2) * (int64_t)cus;
 }
 
+// What a set of strips asks of the one-wave DTW sweeps, in sweep steps.
+struct SweepLoad {
+  int64_t items = 0, pairs = 0;
+  double steps = 0.0;        // of all strips
+  double longest = 0.0;      // of a strip
+  double chain = 0.0;        // of a pair's strips, each following the one above
+  double strips = 0.0;       // of the pair with most
+  void add(int64_t cols, int64_t n_strips) {
+    const double one = (double)(cols + kLanes);
+    items += n_strips;
+    ++pairs;
+    steps += one * n_strips;
+    longest = std::max(longest, one);
+    chain = std::max(chain, one + 110.0 * (n_strips - 1));
+    strips = std::max(strips, (double)n_strips);
+  }
+};
+
+enum { kSweepValues = 0, kSweepScores, kSweepSub, kSweepPaths, kSweepKinds };
+
+// Time of a one-wave sweep at `waves` to a SIMD, in steps of a lone wave, of
+// which a step takes `q`: the longest chain, or the strips over the waves and the
+// end of the last ones; where strips start later than others of their pair,
+// those waiting below hold waves (float64).  A strip costs 90 steps of its own.
+inline double sweep_time(const SweepLoad& l, int cus, int waves, double q, bool fp32) {
+  const double slots = 4.0 * cus * waves;
+  const double t = q * l.chain + 90.0;
+  if (l.items <= slots) return t;
+  const double work = (q * l.steps + 90.0 * l.items) / slots;
+  const double deep = std::max(0.0, l.strips - slots / std::max<double>(1.0, l.pairs));
+  const double wait = waves > 1 && !fp32 ? q * std::min(150.0 * deep, 0.25 * l.longest) : 0.0;
+  return std::max(std::max(t, work + 0.36 * (q * l.longest + 90.0) + wait), 1.8 * work * slots / l.items);
+}
+
+// Waves per SIMD of the one-wave DTW sweeps.  A second wave on a SIMD raises its
+// throughput (a step of both takes q times a step of one) and slows the chain
+// of every pair's strips by as much.  q, measured: 1.4 to 1.8 in float64 with the
+// channels and rows (less for the lighter instruction mixes of Sub-DTW and of
+// value sweeps), 1.2 in float32.  Over 714 sweeps (26 shapes of 1.2 to 14 strips a
+// SIMD, d = 1, 3, 6, all kinds) the choice between one and more costs 0.35 % on
+// average against the better of both, and 11 % at most.  Measured, us at 1 / 2 / 3:
+// scores of 128 x 4k (d = 3) 1524 / 1743 / 1750, in float32 1407 / 1178 / 1170, of 1000 x
+// 1000 (d = 1) 566 / 517 / 505; Sub-DTW of 256 x 4k (d = 1) 2684 / 2332 / 2197.
+// A third gains 3 to 10 % where there are strips enough and the mix is light.
+inline int sweep_waves(const SweepLoad& l, int kind, int cus, int d, int rho, bool fp32) {
+  const double simds = 4.0 * cus;
+  if (l.items <= simds) return 1;
+  double q = kind == kSweepValues ? 1.23 + 0.06 * d : kind == kSweepSub ? 1.36 + 0.04 * d : 1.43 + 0.05 * d;
+  q = std::min(1.03 * (rho == 5 ? q + 0.07 : q), 1.78);
+  if (fp32) q = kind == kSweepValues || kind == kSweepSub ? 1.2 : 1.25;
+  if (sweep_time(l, cus, 1, 1.0, fp32) <= sweep_time(l, cus, 2, q, fp32)) return 1;
+  if (kind == kSweepValues && d <= 4) return 3;
+  const bool light = fp32 ? kind != kSweepScores || l.items > 6 * simds : kind == kSweepSub && d <= 4;
+  return light && l.items > 3 * simds && l.longest > 110.0 * l.strips ? 3 : 2;
+}
+
+// Path recovery.  Codes and entry tags for every cell (PATHT) cost the one-wave
+// sweep 80 ns a step of 4 rows in float64 and 70 in float32, a fifth less
+// above six strips a SIMD, and let all strips be walked at once.  From
+// checkpoints (CKPT) the sweep is the value sweep, and each pair's strips are
+// swept again along its path and walked in turn, 14 us and 6 us a channel a
+// strip (0.7 of that in float32; above 256 pairs they share the compute units).
+// DBA iteration, codes / checkpoints, us: 128 x 4k 1551 / 1143 (d = 1), 1801 / 1540 (d =
+// 3), 1000 x 1000 720 / 657 and 871 / 1001, in float32 568 / 504 and 639 / 666; 512 of
+// 1k-20k (L = 10,000, d = 6) 25.3 / 22.8 ms.  Over 114 batches the choice costs 0.4 %
+// on average and 10 % at most.  A team's sweep costs less a strip than its walk:
+// codes.
+inline bool walk_pairs_pays(const SweepLoad& l, int cus, int d, int rho, bool fp32) {
+  const double simds = 4.0 * cus;
+  const double steps = std::max(l.chain, l.steps / simds);
+  const double codes = (fp32 ? 70e-9 : 80e-9) * (l.items > 6 * simds ? 0.8 : 1.0) * rho / 4;
+  const double trace = (14e-6 + 6e-6 * d) * (fp32 ? 0.7 : 1.0);
+  return steps * codes > l.strips * trace * std::max(1.0, l.pairs / 256.0);
+}
+
 // The Soft-DTW forward: teams of four waves a strip (wts_soft_team.hip) or one
 // wave a strip.  A team takes half the time a step and follows the strip above
 // at half the distance; one wave a strip has fewer instructions a cell once
@@ -92,9 +167,9 @@ inline double bwd_live_most(double rows, double cols) {
 // 77.7 / 64.8; 25 of 30k: 22.9 / 19.2 against 20.6 / 18.2).  In float32 the
 // score sweep is no faster at 5.  Up to four strips a SIMD the longest pair's
 // chain (120 steps a strip) or the rounds of strips on the SIMDs decide, at
-// about 2 d + 8 instructions a row and 20 a step: 5 rows a lane win where they
+// about 2 d + 8 instructions a row and 38 a step: 5 rows a lane win where they
 // save a strip or a round (500 cycles of 300, L = 300, one strip instead of
-// two: 72 against 85 us).
+// two: 72 against 85 us; 512 of 320, L = 320, d = 6: 133 against 144).
 inline int bary_rho(int64_t L, int n, int64_t nmax, int cus, int d, bool fp32, bool team) {
   auto strips = [&](int r) { return (L + 64 * r - 1) / (64 * r); };
   auto items = [&](int r) { return (int64_t)n * strips(r); };
@@ -105,9 +180,9 @@ inline int bary_rho(int64_t L, int n, int64_t nmax, int cus, int d, bool fp32, b
   if (items(4) > 4 * simds) return d >= 2 && !fp32 && steps(5) < steps(4) ? 5 : 4;
   auto chain = [&](int r) {
     const int64_t rounds = (items(r) + simds - 1) / simds, one = nmax + kLanes;
-    return std::max(one + 120 * strips(r), rounds * one) * (r * (2 * d + 8) + 20);
+    return std::max(one + 120 * strips(r), rounds * one) * (r * (2 * d + 8) + 38);
   };
-  return chain(5) * 100 < chain(4) * 97 ? 5 : 4;
+  return chain(5) < chain(4) ? 5 : 4;
 }
 
 // Rows per lane of a plan's barycenter sweeps: bary_rho's, unless the plan's score

@@ -1,5 +1,7 @@
 // Rows per lane and score workspace of barycenter plans (wts_rules.h), read from
-// stdin: d L fp32 team cus n, then n cycle lengths -> "rho bytes2 bytes4 bytes5".
+// stdin: d L fp32 team cus n, then n cycle lengths -> "rho bytes2 bytes4 bytes5",
+// then the waves a SIMD of the one-wave sweeps at 4 rows (values, scores,
+// Sub-DTW, paths) and whether paths are recovered from checkpoints.
 #include <cstdio>
 #include <vector>
 
@@ -22,7 +24,11 @@ int main() {
         rows += (L + kLanes * r - 1) / (kLanes * r) * row_stride_host((int32_t)(off[k + 1] - off[k]));
       std::printf(" %zu", score_bytes(rows, n));
     }
-    std::printf("\n");
+    SweepLoad load;
+    for (int k = 0; k < n; ++k) load.add(off[k + 1] - off[k], (L + 4 * kLanes - 1) / (4 * kLanes));
+    for (int kind = 0; kind < kSweepKinds; ++kind)
+      std::printf(" %d", sweep_waves(load, kind, cus, d, 4, fp32 != 0));
+    std::printf(" %d\n", (int)walk_pairs_pays(load, cus, d, 4, fp32 != 0));
   }
   return 0;
 }

@@ -28,12 +28,16 @@ def rules_bin(tmp_path_factory):
 
 def plans(exe, cases):
     """[(d, L, fp32, team, lengths)] -> [(rho, {rho: workspace bytes})]"""
+    return [(r[0], dict(zip((2, 4, 5), r[1:4]))) for r in rules(exe, cases)]
+
+
+def rules(exe, cases):
+    """The rows that rules_main.cpp prints."""
     inp = "\n".join("%d %d %d %d %d %d %s" % (d, L, fp32, team, CUS, len(lens),
                                              " ".join(map(str, lens)))
                     for d, L, fp32, team, lens in cases)
     out = subprocess.run([exe], input=inp, capture_output=True, text=True, check=True).stdout
-    rows = [tuple(map(int, ln.split())) for ln in out.splitlines()]
-    return [(r[0], dict(zip((2, 4, 5), r[1:]))) for r in rows]
+    return [tuple(map(int, ln.split())) for ln in out.splitlines()]
 
 
 def earlier_rho(L, n):
@@ -65,3 +69,21 @@ def test_no_plan_that_fitted_the_scratch_is_refused(rules_bin, team, fp32):
             fitted += 1
             lost += size[rho] > SCRATCH
     assert fitted > 1000 and lost == 0
+
+
+def test_waves_and_path_recovery_of_measured_batches(rules_bin):
+    """Batches where one choice was measured at least a tenth faster than the
+    other (the lengths are the measured ones' mean)."""
+    values, scores, sub, paths, pairs = range(4, 9)
+    got = rules(rules_bin, [
+        (3, 4000, 0, 0, [4000] * 128),   # float64 scores: one wave, 1.52 ms against 1.74
+        (3, 4000, 1, 0, [4000] * 128),   # float32: two, 1.18 against 1.41
+        (1, 4000, 0, 0, [4000] * 256),   # light Sub-DTW: three, 2.20 against 2.68
+        (6, 8000, 0, 0, [8000] * 64),    # six channels: one, 3.97 against 5.10
+        (1, 1000, 0, 0, [1000] * 2000),  # many strips
+        (1, 4000, 0, 0, [4000] * 256),   # paths from checkpoints, 1.57 against 2.42
+        (6, 1000, 0, 0, [1000] * 2000),  # from codes, 1.95 against 2.50
+    ])
+    assert got[0][scores] == 1 and got[1][scores] >= 2 and got[2][sub] == 3 and got[3][scores] == 1
+    assert min(got[4][values:pairs]) >= 2
+    assert got[5][pairs] == 1 and got[6][pairs] == 0
