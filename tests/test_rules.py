@@ -73,16 +73,20 @@ def test_no_plan_that_fitted_the_scratch_is_refused(rules_bin, team, fp32):
 
 def test_waves_and_path_recovery_of_measured_batches(rules_bin):
     """Batches where one choice was measured at least a tenth faster than the
-    other (the lengths are the measured ones' mean)."""
+    other; n lengths even between 0.8 N and 1.2 N."""
     values, scores, sub, paths, pairs = range(4, 9)
+
+    def lens(n, N):
+        return np.random.default_rng(0).integers(int(0.8 * N), int(1.2 * N) + 1, n).tolist()
+
     got = rules(rules_bin, [
-        (3, 4000, 0, 0, [4000] * 128),   # float64 scores: one wave, 1.52 ms against 1.74
-        (3, 4000, 1, 0, [4000] * 128),   # float32: two, 1.18 against 1.41
-        (1, 4000, 0, 0, [4000] * 256),   # light Sub-DTW: three, 2.20 against 2.68
-        (6, 8000, 0, 0, [8000] * 64),    # six channels: one, 3.97 against 5.10
-        (1, 1000, 0, 0, [1000] * 2000),  # many strips
-        (1, 4000, 0, 0, [4000] * 256),   # paths from checkpoints, 1.57 against 2.42
-        (6, 1000, 0, 0, [1000] * 2000),  # from codes, 1.95 against 2.50
+        (3, 4000, 0, 0, lens(128, 4000)),   # float64 scores: one wave, 1.52 ms against 1.74
+        (3, 4000, 1, 0, lens(128, 4000)),   # float32: two, 1.18 against 1.41
+        (1, 4000, 0, 0, lens(256, 4000)),   # light Sub-DTW: three, 2.20 against 2.68
+        (6, 8000, 0, 0, lens(64, 8000)),    # six channels: one, 3.97 against 5.10
+        (1, 1000, 0, 0, lens(2000, 1000)),  # many strips
+        (1, 4000, 0, 0, lens(256, 4000)),   # paths from checkpoints, 1.57 against 2.42
+        (6, 1000, 0, 0, lens(2000, 1000)),  # from codes, 1.95 against 2.50
     ])
     assert got[0][scores] == 1 and got[1][scores] >= 2 and got[2][sub] == 3 and got[3][scores] == 1
     assert min(got[4][values:pairs]) >= 2
