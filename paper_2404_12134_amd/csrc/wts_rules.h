@@ -48,11 +48,13 @@ struct SweepLoad {
   int64_t items = 0, pairs = 0;
   double steps = 0.0;        // of all strips
   double longest = 0.0;      // of a strip
+  double shortest = 0.0;
   double chain = 0.0;        // of a pair's strips, each following the one above
   double strips = 0.0;       // of the pair with most
   void add(int64_t cols, int64_t n_strips) {
     const double one = (double)(cols + kLanes);
     items += n_strips;
+    shortest = pairs == 0 ? one : std::min(shortest, one);
     ++pairs;
     steps += one * n_strips;
     longest = std::max(longest, one);
@@ -65,34 +67,38 @@ enum { kSweepValues = 0, kSweepScores, kSweepSub, kSweepPaths, kSweepKinds };
 
 // Time of a one-wave sweep at `waves` to a SIMD, in steps of a lone wave, of
 // which a step takes `q`: the longest chain, or the strips over the waves and the
-// end of the last ones; where strips start later than others of their pair,
-// those waiting below hold waves (float64).  A strip costs 90 steps of its own.
+// end of the last ones (the longer the more the pairs' lengths differ); where
+// strips start later than others of their pair, those waiting below hold waves
+// (float64).  A strip costs 120 steps of its own.
 inline double sweep_time(const SweepLoad& l, int cus, int waves, double q, bool fp32) {
   const double slots = 4.0 * cus * waves;
-  const double t = q * l.chain + 90.0;
+  const double t = q * l.chain + 120.0;
   if (l.items <= slots) return t;
-  const double work = (q * l.steps + 90.0 * l.items) / slots;
-  const double deep = std::max(0.0, l.strips - slots / std::max<double>(1.0, l.pairs));
-  const double wait = waves > 1 && !fp32 ? q * std::min(150.0 * deep, 0.25 * l.longest) : 0.0;
-  return std::max(std::max(t, work + 0.36 * (q * l.longest + 90.0) + wait), 1.8 * work * slots / l.items);
+  const double work = (q * l.steps + 120.0 * l.items) / slots;
+  const double tail = q * std::min(0.36 * l.longest, 2.0 * (l.longest - l.steps / l.items));
+  const double deep = std::max(0.0, l.strips - slots / l.pairs);
+  const double wait = waves > 1 && !fp32 ? q * std::min(250.0 * deep, 0.25 * l.longest) : 0.0;
+  const double rounds = std::ceil(l.items / slots) * (q * l.shortest + 120.0);
+  return std::max(std::max(t, work + tail + wait), rounds);
 }
 
 // Waves per SIMD of the one-wave DTW sweeps.  A second wave on a SIMD raises its
 // throughput (a step of both takes q times a step of one) and slows the chain
 // of every pair's strips by as much.  q, measured: 1.4 to 1.8 in float64 with the
 // channels and rows (less for the lighter instruction mixes of Sub-DTW and of
-// value sweeps), 1.2 in float32.  Over 714 sweeps (26 shapes of 1.2 to 14 strips a
-// SIMD, d = 1, 3, 6, all kinds) the choice between one and more costs 0.35 % on
-// average against the better of both, and 11 % at most.  Measured, us at 1 / 2 / 3:
-// scores of 128 x 4k (d = 3) 1524 / 1743 / 1750, in float32 1407 / 1178 / 1170, of 1000 x
-// 1000 (d = 1) 566 / 517 / 505; Sub-DTW of 256 x 4k (d = 1) 2684 / 2332 / 2197.
+// value sweeps), 1.1 in float32.  Over 786 sweeps (32 shapes of 1.2 to 14 strips a
+// SIMD, of lengths that spread by half and of equal ones, d = 1, 3, 6, all kinds) the
+// choice between one and more costs 0.24 % on average against the better of
+// both, and 18 % at most.  Measured, us at 1 / 2 / 3: scores of 128 cycles of about 4k
+// (d = 3) 1524 / 1743 / 1750, in float32 1407 / 1178 / 1170, of 1000 of 1000 (d = 1)
+// 566 / 517 / 505; Sub-DTW of 256 of 4k (d = 1) 2684 / 2332 / 2197.
 // A third gains 3 to 10 % where there are strips enough and the mix is light.
 inline int sweep_waves(const SweepLoad& l, int kind, int cus, int d, int rho, bool fp32) {
   const double simds = 4.0 * cus;
   if (l.items <= simds) return 1;
   double q = kind == kSweepValues ? 1.23 + 0.06 * d : kind == kSweepSub ? 1.36 + 0.04 * d : 1.43 + 0.05 * d;
   q = std::min(1.03 * (rho == 5 ? q + 0.07 : q), 1.78);
-  if (fp32) q = kind == kSweepValues || kind == kSweepSub ? 1.2 : 1.25;
+  if (fp32) q = kind == kSweepValues || kind == kSweepSub ? 1.1 : 1.15;
   if (sweep_time(l, cus, 1, 1.0, fp32) <= sweep_time(l, cus, 2, q, fp32)) return 1;
   if (kind == kSweepValues && d <= 4) return 3;
   const bool light = fp32 ? kind != kSweepScores || l.items > 6 * simds : kind == kSweepSub && d <= 4;

@@ -91,3 +91,16 @@ def test_waves_and_path_recovery_of_measured_batches(rules_bin):
     assert got[0][scores] == 1 and got[1][scores] >= 2 and got[2][sub] == 3 and got[3][scores] == 1
     assert min(got[4][values:pairs]) >= 2
     assert got[5][pairs] == 1 and got[6][pairs] == 0
+
+
+def test_waves_of_equal_lengths(rules_bin):
+    """Strips of equal lengths end together: a second wave on a SIMD of three
+    strips was measured to cost there, us at one / two waves."""
+    scores, sub = 5, 6
+    got = rules(rules_bin, [
+        (3, 4000, 0, 0, [4000] * 128),   # float64 scores 1390 / 1674
+        (6, 4000, 0, 0, [4000] * 128),   # Sub-DTW 2043 / 2430
+        (6, 8000, 0, 0, [8000] * 64),    # 4034 / 5069
+        (3, 4000, 1, 0, [4000] * 128),   # float32: two
+    ])
+    assert got[0][scores] == 1 and got[1][sub] == 1 and got[2][sub] == 1 and got[3][scores] >= 2
