@@ -111,7 +111,7 @@ typedef struct {
                          the medoid always use the squared cost                              */
   int32_t rho;        /* rows per lane in the wavefront sweeps: 0 = automatic (2 for barycenter
                          plans of few strips, which teams of four waves a strip sweep; 4, or 5
-                         where that balances the strips better, else); 2, 4 or 5 for any plan
+                         where that was measured faster, else); 2, 4 or 5 for any plan
                          (Soft-DTW sweeps always use 2); other values return
                          WTS_E_UNSUPPORTED                                                   */
   int32_t grid;       /* waves of the persistent one-wave-a-strip sweep (0 = tuned default, and
@@ -266,8 +266,10 @@ wts_status wts_anomaly_score(const wts_plan* plan, const double* bary, const voi
  * workspace -- a static device array of 32 MiB that each GPU the library
  * runs on holds until the process ends (its address on a GPU is resolved by
  * wts_plan_create on that GPU).  Arguments, results and errors are those of
- * wts_anomaly_score; WTS_E_CAPACITY when the plan's score workspace
- * (wts_workspace_bytes(plan, WTS_OP_SCORE)) exceeds 32 MiB.  It calls no
+ * wts_anomaly_score; WTS_E_CAPACITY when its score sweep needs more than
+ * 32 MiB.  Where the plan's score workspace (wts_workspace_bytes(plan,
+ * WTS_OP_SCORE)) does, and the sweep with more rows a lane needs less, this
+ * call takes that one (opts.rho = 0 only; same results).  It calls no
  * allocating routine.  Every call on one GPU uses that GPU's one scratch:
  * calls that overlap on a GPU (two streams, two host threads) race and give
  * undefined results; the scratch keeps the last call's contents, and each

@@ -184,6 +184,7 @@ struct wts_plan {
   int2* d_med_ab = nullptr;
   PairSet bary, med, soft;
   PairSet softT;   // Soft-DTW with the roles swapped: the cycles on the rows, B on the columns
+  PairSet tight;   // bary with the rows of scratch_rho, for wts_anomaly_score_noalloc; else empty
   int64_t nmax = 0;
   // device words: [0] sticky status bits (wts_plan_status reads and clears
   // them), [1] the current call's validation flag, [2] read-out slot
@@ -197,11 +198,12 @@ struct wts_plan {
 
 namespace {
 
-Layout layout(const wts_plan* p, int op) {
+Layout layout(const wts_plan* p, int op, const PairSet* set = nullptr) {
   Layout l;
   size_t o = 0;
   auto take = [&](size_t bytes) { size_t at = o; o = align_up(o + std::max<size_t>(bytes, 1)); return at; };
-  const PairSet& ps = op == WTS_OP_MEDOID ? p->med
+  const PairSet& ps = set != nullptr ? *set
+                      : op == WTS_OP_MEDOID ? p->med
                       : (op == WTS_OP_SOFT_FWD || op == WTS_OP_SOFT_BWD) ? p->soft
                       : op == WTS_OP_SOFT_GRAD_C ? p->softT : p->bary;
   if (op == WTS_OP_SOFT_GRAD_C) {   // the transposed forward and backward in one buffer
@@ -470,6 +472,22 @@ wts_status run_paths(const wts_plan* p, const double* bary, const void* cycles, 
   return WTS_OK;
 }
 
+// The score sweep of one of the plan's barycenter sets, and Eq. 8.
+wts_status run_score(const wts_plan* p, const PairSet& ps, const double* bary, const void* cycles,
+                     double* score, double* dist, int64_t* path_len, void* ws, void* stream) {
+  DeviceGuard g(p->device);
+  hipStream_t st = static_cast<hipStream_t>(stream);
+  wts_status rc = validate_inputs(p, st, seg_f64(bary, p->L * p->d), seg_cycles(p, cycles));
+  if (rc != WTS_OK) return rc;
+  const Layout l = layout(p, WTS_OP_SCORE, &ps);
+  double* dv = dist ? dist : at<double>(ws, l.out_dist);
+  rc = run_sweep(p, ps, wts::MODE_DIST_LEN, p->opts.cost == WTS_COST_EUCLID, false, bary, cycles,
+                 ws, l, dv, st);
+  if (rc != WTS_OK) return rc;
+  HIP_TRY(wts::launch_score(dv, at<int>(ws, l.out_aux), p->n, score, path_len, st));
+  return WTS_OK;
+}
+
 }  // namespace
 
 extern "C" {
@@ -546,11 +564,15 @@ wts_status wts_plan_create(wts_plan** out, int device, int32_t n, int32_t d, int
       jobs.push_back(Job{0, p->off[k], (int32_t)L, (int32_t)(p->off[k + 1] - p->off[k]), k});
     const bool fp32 = o.decision == WTS_DECISION_FP32;
     const bool team = o.grid == 0;   // a grid asks for that many one-wave sweepers
-    const int rho = o.rho ? o.rho : plan_rho(p->off.data(), n, L, p->cus, d, fp32, team);
+    const int rho = o.rho ? o.rho : bary_rho(L, n, p->nmax, p->cus, d, fp32, team);
+    const int less = o.rho ? 0 : scratch_rho(rho, p->off.data(), n, L, p->cus, d, fp32);
     build_set(p->bary, jobs, rho, false);
-    p->bary.team = team && team_pays(p->bary.rho, p->bary.n_items, p->cus, fp32);
-    for (int kind : {kSweepScores, kSweepSub, kSweepPaths})
-      p->bary.waves[kind] = sweep_waves(p->bary.load, kind, p->cus, d, rho, fp32);
+    if (less) build_set(p->tight, jobs, less, false);
+    for (PairSet* ps : {&p->bary, &p->tight}) {
+      ps->team = team && team_pays(ps->rho, ps->n_items, p->cus, fp32);
+      for (int kind : {kSweepScores, kSweepSub, kSweepPaths})
+        ps->waves[kind] = sweep_waves(ps->load, kind, p->cus, d, ps->rho, fp32);
+    }
     p->bary.walk_pairs = o.walk == WTS_WALK_PAIRS ||
                          (o.walk == WTS_WALK_AUTO && !p->bary.team &&
                           walk_pairs_pays(p->bary.load, p->cus, d, rho, fp32));
@@ -589,7 +611,7 @@ wts_status wts_plan_create(wts_plan** out, int device, int32_t n, int32_t d, int
         return cleanup_fail(e, "hipMemcpy");
     }
   }
-  for (PairSet* ps : {&p->bary, &p->med, &p->soft, &p->softT}) {
+  for (PairSet* ps : {&p->bary, &p->tight, &p->med, &p->soft, &p->softT}) {
     if (ps->pairs.empty()) continue;
     hipError_t e;
     if ((e = hipMalloc(&ps->d_pairs, sizeof(PairDesc) * ps->pairs.size())) != hipSuccess) return cleanup_fail(e, "hipMalloc");
@@ -605,7 +627,7 @@ wts_status wts_plan_create(wts_plan** out, int device, int32_t n, int32_t d, int
     if ((e = hipMemcpy(ps->d_items, ps->items.data(), sizeof(int2) * ps->items.size(), hipMemcpyHostToDevice)) != hipSuccess)
       return cleanup_fail(e, "hipMemcpy");
   }
-  for (PairSet* ps : {&p->bary, &p->med, &p->soft, &p->softT})
+  for (PairSet* ps : {&p->bary, &p->tight, &p->med, &p->soft, &p->softT})
     if (ps->items.size() > (size_t(1) << 30)) {
       wts_plan_destroy(p);
       return fail(WTS_E_CAPACITY, "more than 2^30 sweep items (pairs x strips)");
@@ -705,7 +727,7 @@ void wts_plan_destroy(wts_plan* p) {
   if (!p) return;
   DeviceGuard g(p->device);
   for (hipEvent_t e : p->ev) (void)hipEventDestroy(e);
-  for (PairSet* ps : {&p->bary, &p->med, &p->soft, &p->softT}) {
+  for (PairSet* ps : {&p->bary, &p->tight, &p->med, &p->soft, &p->softT}) {
     if (ps->d_pairs) (void)hipFree(ps->d_pairs);
     if (ps->d_items) (void)hipFree(ps->d_items);
     if (ps->d_items_rev) (void)hipFree(ps->d_items_rev);
@@ -795,17 +817,7 @@ wts_status wts_anomaly_score(const wts_plan* p, const double* bary, const void* 
   if (rc != WTS_OK) return rc;
   if (!bary || !cycles || !score) return fail(WTS_E_ARG, "null bary/cycles/score");
   if ((rc = check_ws(p, WTS_OP_SCORE, ws, ws_bytes)) != WTS_OK) return rc;
-  DeviceGuard g(p->device);
-  hipStream_t st = static_cast<hipStream_t>(stream);
-  if ((rc = validate_inputs(p, st, seg_f64(bary, p->L * p->d), seg_cycles(p, cycles))) != WTS_OK)
-    return rc;
-  const Layout l = layout(p, WTS_OP_SCORE);
-  double* dv = dist ? dist : at<double>(ws, l.out_dist);
-  rc = run_sweep(p, p->bary, wts::MODE_DIST_LEN, p->opts.cost == WTS_COST_EUCLID, false, bary,
-                 cycles, ws, l, dv, st);
-  if (rc != WTS_OK) return rc;
-  HIP_TRY(wts::launch_score(dv, at<int>(ws, l.out_aux), p->n, score, path_len, st));
-  return WTS_OK;
+  return run_score(p, p->bary, bary, cycles, score, dist, path_len, ws, stream);
 }
 
 wts_status wts_anomaly_score_noalloc(const wts_plan* p, const double* bary, const void* cycles,
@@ -813,7 +825,8 @@ wts_status wts_anomaly_score_noalloc(const wts_plan* p, const double* bary, cons
                                      void* stream) {
   wts_status rc = check_bary_plan(p);
   if (rc != WTS_OK) return rc;
-  const size_t need = layout(p, WTS_OP_SCORE).total;
+  const PairSet& ps = p->tight.pairs.empty() ? p->bary : p->tight;
+  const size_t need = layout(p, WTS_OP_SCORE, &ps).total;
   if (need > kScratchBytes)
     return fail(WTS_E_CAPACITY, "the score sweep of this plan needs %zu bytes of workspace; "
                 "the static scratch holds %zu", need, kScratchBytes);
@@ -823,7 +836,8 @@ wts_status wts_anomaly_score_noalloc(const wts_plan* p, const double* bary, cons
     if (p->device >= 0 && p->device < kMaxDevices) ws = g_scratch[p->device];
   }
   if (ws == nullptr) return fail(WTS_E_HIP, "no scratch address for device %d", p->device);
-  return wts_anomaly_score(p, bary, cycles, score, dist, path_len, ws, kScratchBytes, stream);
+  if (!bary || !cycles || !score) return fail(WTS_E_ARG, "null bary/cycles/score");
+  return run_score(p, ps, bary, cycles, score, dist, path_len, ws, stream);
 }
 
 wts_status wts_subdtw(const wts_plan* p, const double* x, const void* windows, double* value,

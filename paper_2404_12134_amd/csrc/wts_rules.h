@@ -191,14 +191,13 @@ inline int bary_rho(int64_t L, int n, int64_t nmax, int cus, int d, bool fp32, b
   return chain(5) < chain(4) ? 5 : 4;
 }
 
-// Rows per lane of a plan's barycenter sweeps: bary_rho's, unless the plan's score
-// workspace then exceeds the scratch of wts_anomaly_score_noalloc and fewer
-// strip rows (more rows a lane) would fit it: those of the one-wave sweeps, or 5
-// where that brings more strips than 13/16 of the SIMDs, and at most two a
-// SIMD, under 13/16.  That was once the rule for 5 rows, and a plan that
-// fitted by it (14 cycles of 3000, L = 17,560: 28 MB against 35 at 4) still does.
-// off: n + 1 offsets.
-inline int plan_rho(const int64_t* off, int n, int64_t L, int cus, int d, bool fp32, bool team) {
+// Rows per lane of wts_anomaly_score_noalloc where the plan's own (rho) need more
+// workspace than its scratch holds and fewer strip rows (more rows a lane) fit it:
+// those of the one-wave sweeps, or 5 where that brings more strips than 13/16 of
+// the SIMDs, and at most two a SIMD, under 13/16.  That was once the rule for 5
+// rows, and a batch that fitted by it (14 cycles of 3000, L = 17,560: 28 MB
+// against 35 at 4) still does.  0: the plan's own rows.  off: n + 1 offsets.
+inline int scratch_rho(int rho, const int64_t* off, int n, int64_t L, int cus, int d, bool fp32) {
   int64_t nmax = 0;
   for (int k = 0; k < n; ++k) nmax = std::max(nmax, off[k + 1] - off[k]);
   auto strips = [&](int r) { return (L + kLanes * r - 1) / (kLanes * r); };
@@ -207,14 +206,12 @@ inline int plan_rho(const int64_t* off, int n, int64_t L, int cus, int d, bool f
     for (int k = 0; k < n; ++k) rows += strips(r) * row_stride_host((int32_t)(off[k + 1] - off[k]));
     return score_bytes(rows, n) <= kScratchBytes;
   };
-  const int rho = bary_rho(L, n, nmax, cus, d, fp32, team);
-  if (fits(rho)) return rho;
+  if (fits(rho)) return 0;
   const int alt = bary_rho(L, n, nmax, cus, d, fp32, false);
   if (alt != rho && fits(alt)) return alt;
   const int64_t simds = 4 * (int64_t)cus, cap = simds * 13 / 16;
   const int64_t i4 = n * strips(4);
-  if (i4 > cap && i4 <= 2 * simds && n * strips(5) <= cap && fits(5)) return 5;
-  return rho;
+  return i4 > cap && i4 <= 2 * simds && n * strips(5) <= cap && fits(5) ? 5 : 0;
 }
 
 }  // namespace rules

@@ -1,7 +1,8 @@
 // Rows per lane and score workspace of barycenter plans (wts_rules.h), read from
-// stdin: d L fp32 team cus n, then n cycle lengths -> "rho bytes2 bytes4 bytes5",
-// then the waves a SIMD of the one-wave sweeps at 4 rows (values, scores,
-// Sub-DTW, paths) and whether paths are recovered from checkpoints.
+// stdin: d L fp32 team cus n, then n cycle lengths -> "rho bytes2 bytes4 bytes5"
+// (rho: of the non-allocating score call), then the waves a SIMD of the one-wave
+// sweeps at 4 rows (values, scores, Sub-DTW, paths) and whether paths are
+// recovered from checkpoints.
 #include <cstdio>
 #include <vector>
 
@@ -17,7 +18,11 @@ int main() {
       if (std::scanf("%lld", &len) != 1) return 2;
       off.push_back(off.back() + len);
     }
-    std::printf("%d", plan_rho(off.data(), n, L, cus, d, fp32 != 0, team != 0));
+    int64_t nmax = 0;
+    for (int k = 0; k < n; ++k) nmax = std::max(nmax, off[k + 1] - off[k]);
+    const int rho = bary_rho(L, n, nmax, cus, d, fp32 != 0, team != 0);
+    const int less = scratch_rho(rho, off.data(), n, L, cus, d, fp32 != 0);
+    std::printf("%d", less ? less : rho);
     for (int r : {2, 4, 5}) {
       int64_t rows = 0;
       for (int k = 0; k < n; ++k)

@@ -1,7 +1,7 @@
-"""The rows per lane a barycenter plan takes (csrc/wts_rules.h), built with the
-host compiler: a plan whose score workspace fitted the scratch of the
-non-allocating score entry point with the rows of the earlier rule (4, or 5
-where that brings more than 13/16 of the SIMDs' strips under it) still fits."""
+"""The rules by which a barycenter plan chooses its sweeps (csrc/wts_rules.h), built
+with the host compiler.  Rows per lane of the non-allocating score call: a plan
+whose score workspace fitted its scratch with the rows of the earlier rule (4, or
+5 where that brings more than 13/16 of the SIMDs' strips under it) still fits."""
 import os
 import shutil
 import subprocess
