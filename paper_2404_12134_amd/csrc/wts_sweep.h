@@ -108,10 +108,12 @@ __device__ __forceinline__ void wave_sync() {
 // TC = double is the float64 recurrence; TC = float runs the same steps in
 // float32 (X rounded to float32 once, float32 cycles as they are): the
 // float32-decision variant.
-// The value sweep (medoid) runs on many items at once and is held to five
-// resident wavefronts per SIMD; the other modes keep their registers.
+// The value sweep (medoid) of up to four channels runs at up to three waves to a
+// SIMD (sweep_waves), and its registers are held to that; the other modes keep
+// theirs.  Held to five, it spilled: 64 cycles of about 2000 (d = 3) 2.98 -> 2.92
+// ms, 40 of 4000 (d = 4) 5.69 -> 5.48, in float32 the same.
 template <typename TX, typename TY, typename TC, int D, int RHO, int MODE, bool EUC>
-__global__ __launch_bounds__(kWave * kSweepWaves, MODE == MODE_DIST && D <= 4 ? 5 : 1)
+__global__ __launch_bounds__(kWave * kSweepWaves, MODE == MODE_DIST && D <= 4 ? 3 : 1)
 void dtw_fwd_kernel(FwdArgs a) {
   constexpr int H = kWave * RHO;
   // tags carried along the argmin: the path length (DIST_LEN), the start
