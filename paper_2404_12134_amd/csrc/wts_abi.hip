@@ -421,9 +421,8 @@ wts_status run_sweep(const wts_plan* p, const PairSet& ps, int mode, bool euc, b
                                  : mode == wts::MODE_CKPT || mode == wts::MODE_PATHT ? WTS_OP_DBA
                                  : mode == wts::MODE_SUB ? WTS_OP_SUBDTW : WTS_OP_SCORE, st);
   const bool fp32 = p->opts.decision == WTS_DECISION_FP32;
-  if (ps.team)   // at most the four workgroups a compute unit holds, and twice as many waiting
-    HIP_TRY(wts::launch_team(p->d, ps.rho, mode, euc, x_is_cycle, p->dtype, fp32, a,
-                             std::min(ps.n_items, 8 * p->cus), st));
+  if (ps.team)   // a workgroup a strip: team_pays admits five a compute unit at most
+    HIP_TRY(wts::launch_team(p->d, ps.rho, mode, euc, x_is_cycle, p->dtype, fp32, a, ps.n_items, st));
   else
     HIP_TRY(wts::launch_fwd(p->d, ps.rho, mode, euc, x_is_cycle, p->dtype, fp32, a,
                             dtw_grid(p, ps, waves), st));

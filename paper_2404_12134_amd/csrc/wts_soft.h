@@ -45,16 +45,8 @@ namespace wts {
 
 namespace {
 
-
-__device__ __forceinline__ double shl1_f64(double v, double old) {
-  // DPP wave_shl:1 -- lane k receives v from lane k+1; lane 63 receives `old`.
-  const long long s = __double_as_longlong(v), o = __double_as_longlong(old);
-  const int lo = __builtin_amdgcn_update_dpp((int)o, (int)s, 0x130, 0xf, 0xf, false);
-  const int hi = __builtin_amdgcn_update_dpp((int)(o >> 32), (int)(s >> 32), 0x130, 0xf, 0xf, false);
-  return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
-}
-
 __device__ __forceinline__ float shl1_f32(float v, float old) {
+  // DPP wave_shl:1 -- lane k receives v from lane k+1; lane 63 receives `old`.
   return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(__builtin_bit_cast(int, old),
                                                                __builtin_bit_cast(int, v), 0x130,
                                                                0xf, 0xf, false));

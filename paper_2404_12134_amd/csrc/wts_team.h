@@ -51,6 +51,9 @@ __global__ __launch_bounds__(kWave * kTeamWaves) void dtw_team_kernel(FwdArgs a)
   const TC INF = (TC)inf_d();
   if (skipped(a.skip)) return;   // every workgroup: no strip waits for another
 
+  // Launched with a workgroup a strip, so each takes one and its second pop ends
+  // it.  Built without the loop the kernel was slower where teams share compute
+  // units: scores of 32 x 4.4k (L = 4000, d = 6) 925 -> 1049 us.
   for (;;) {
     if (threadIdx.x == 0) s_item = atomicAdd(a.queue, 1);
     __syncthreads();
