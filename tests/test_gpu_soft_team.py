@@ -40,3 +40,32 @@ def test_team_forward_is_bitwise_the_one_wave_forward(wts, L, band):
     if band == 0.0:
         ov = oracle.softdtw_batch(X, [c.astype(np.float64) for c in cyc], 0.5, grad=False)
         np.testing.assert_allclose(out[0][0], ov, rtol=1e-4)
+
+
+def test_team_forward_of_several_strips_a_workgroup(wts):
+    """More strips than the launch has workgroups (four a compute unit), so that
+    each takes a second one with the same LDS: lengths of every remainder of a
+    group of 16 steps, short strips after long ones."""
+    import torch
+    r = np.random.Generator(np.random.PCG64(77))
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    L, d = 300, 3
+    n = 4 * cus * 2 // 3 + 40               # 3 strips each: over twice 4 a unit
+    lens = r.integers(1, 260, n)
+    X, cyc = r.standard_normal((L, d)), [r.standard_normal((m, d)).astype(np.float32) for m in lens]
+    Y, off, _ = wts.pack_cycles(cyc, dtype="f32")
+    B = torch.from_numpy(X).cuda()
+    gv = torch.from_numpy(r.uniform(0.5, 2.0, n)).cuda()
+    out = []
+    for grid in (0, 512):
+        print("case soft team of many strips n", n, "grid", grid, flush=True)
+        p = wts.Plan(off, d, "f32", L, grid=grid)
+        v, ck = wts.softdtw_forward(p, B, Y, 0.5)
+        g, h = wts.softdtw_backward(p, B, Y, 0.5, ck, gv, with_mass=True)
+        assert p.status() == wts.OK
+        out.append([t.cpu().numpy() for t in (v, g, h)])
+    for a, b in zip(*out):
+        np.testing.assert_array_equal(a, b)
+    pick = list(range(0, n, 25))
+    ov = oracle.softdtw_batch(X, [cyc[k].astype(np.float64) for k in pick], 0.5, grad=False)
+    np.testing.assert_allclose(out[0][0][pick], ov, rtol=1e-4)
