@@ -102,7 +102,7 @@ def kernel_source_hash() -> str:
     h = hashlib.sha256()
     for f in ("wts_sweep.h", "wts_team.h", "wts_walk.h", "wts_trace.h", "wts_dtw.hip",
               "wts_dtw32.hip", "wts_soft.h", "wts_soft.hip", "wts_soft_team.hip",
-              "wts_soft_bwd.hip", "wts_soft_wave.hip", "wts_device.h"):
+              "wts_soft_bwd.hip", "wts_soft_wave.hip", "wts_soft_link.h", "wts_device.h"):
         with open(os.path.join(ROOT, "paper_2404_12134_amd", "csrc", f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()[:16]

@@ -152,9 +152,10 @@ typedef struct {
                          and all strips are then walked at once; WTS_WALK_PAIRS (2): the sweep
                          keeps checkpoints only (a fifth to a third faster), and each pair
                          sweeps the tiles its path crosses again and walks its strips in turn;
-                         WTS_WALK_AUTO (0, default): pairs when the batch's cells outweigh
-                         its longest pair's walk (large batches), else strips.  Paths,
-                         counts and sums are the same bits either way                      */
+                         WTS_WALK_AUTO (0, default): pairs where the codes were measured to
+                         cost more than the longest pairs' walk (long strips, few
+                         channels), else strips.  Paths, counts and sums are the same
+                         bits either way                                                   */
 } wts_opts;
 
 /* Create a plan for a batch of n cycles of d channels (1 <= d <= 8) stored as

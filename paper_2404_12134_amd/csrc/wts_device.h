@@ -175,7 +175,7 @@ __device__ __forceinline__ void poll_backoff(int polls, int relaxed) {
 // Polls of a neighbour's word before a strip gives up (about a second).  A
 // legitimate wait is bounded by one chunk, group or tile of the neighbour; only the
 // wait for the first push in the Soft-DTW backward is longer, and has a limit
-// that grows with the pair (wts_soft_bwd.hip, learn_start).
+// that grows with the pair (BwdLink::learn_start).
 constexpr int kSpinLimit = 1 << 20;
 
 // DPP wave_shr:1 -- lane k receives v from lane k-1; lane 0 receives `old`.

@@ -1,6 +1,7 @@
 // wts_soft.h -- what the Soft-DTW kernels share: Soft-DTW forward (Eq. 3-5;
 // wts_soft.hip and, for batches of few strips, wts_soft_team.hip) and its
-// gradient (Eq. 6; wts_soft_bwd.hip) for gfx950.
+// gradient (Eq. 6; wts_soft_bwd.hip, a workgroup a strip, and wts_soft_wave.hip,
+// one wave a strip; wts_soft_link.h joins the strips) for gfx950.
 //
 // Units.  The cumulative costs are kept scaled, R' = R * k with
 // k = log2(e) / gamma, so the soft-min of Eq. 3 becomes
@@ -23,12 +24,12 @@
 // where w_s(i, j) = 2^(m_s - r'(i, j)) / sum_s is the normalised weight of
 // (i, j) in the soft-min of its successor s, and e(M-1, N-1) = 1 (the cell
 // that closes the path).  The kernel walks each strip's tiles from the last
-// column to the first: some waves replay the tiles forward, leaving the
-// normalised weights of the up and left predecessors of every cell in LDS
-// (float32), another sweeps each tile backwards in "push" form -- each finished
-// cell splits its e over its three predecessors with its own weights, the
-// diagonal taking what the other two do not, so that the split conserves e
-// up to the rounding of one float32 subtraction -- and no cell ever needs a
+// column to the first: a tile is replayed forward, leaving the normalised
+// weights of the up and left predecessors of every cell (float32), and then
+// swept backwards in "push" form (by other waves of the workgroup, or by the
+// same wave) -- each finished cell splits its e over its three predecessors with
+// its own weights, the diagonal taking what the other two do not, so that the
+// split conserves e up to the rounding of one float32 subtraction -- and no cell ever needs a
 // neighbour's weights.  e lies in [0, 1] and travels in float32 (registers,
 // lane shifts, LDS and the push rows between strips).  The pushes of a
 // strip's top row feed the strip above, so strips are pipelined from the

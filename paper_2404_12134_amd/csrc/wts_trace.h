@@ -25,8 +25,8 @@ constexpr int kTraceCols = 64 * kTraceWaves + 64;
 // 0 walks the strip on the scalar unit (walk_strip) and the workgroup goes on
 // with the strip above.  Per row it records the run of columns [lo, hi] the
 // path occupies.  The pairs run in parallel, the strips of a pair in turn, so
-// what bounds it is the latency of one strip (23 us and 2.4 us a channel:
-// wts_abi.hip, walk_pairs_pays): two of the tiles share a SIMD.  With the sweep
+// what bounds it is the latency of one strip (14 us and 6 us a channel up to 256
+// pairs: walk_pairs_pays): two of the tiles share a SIMD.  With the sweep
 // that needs no codes, DBA on 512 cycles of 1k-20k (d = 6) 26.9 -> 22.9 ms, 40
 // of 45k in float32 54.3 -> 43.1 ms.  Sweeping the strip above at a predicted
 // place while a strip is walked gained 4 % there and nothing in float64.
