@@ -390,15 +390,33 @@ __global__ __launch_bounds__(kWave * kBwdWaves) void soft_bwd_kernel(SoftArgs a)
       double acc_e = 0.0, acc_ey[D];
 #pragma unroll
       for (int c = 0; c < D; ++c) acc_ey[c] = 0.0;
+      // The LDS operands of kSum steps ahead of their use: left to the compiler
+      // they are waited for one by one in some instances (band, three channels
+      // or more), and the sums outlast the phase: 5 cycles of 18k (d = 6, band 0.6)
+      // 5.87 ms, so 3.98.  Larger groups hold up the push sweep's own reads: two
+      // steps / four / eight at d = 3 3.49 / 3.55 / 3.59 ms, two / four at d = 6 with
+      // the band 4.08 / 3.98.
+      constexpr int kSum = D <= 5 ? 2 : 4;
       auto add_tile = [&](int g, int b) {   // cells outside the grid have e = 0 and y = 0
         const int yb = (16 * g - lane) & (kBwdRing - 1);
 #pragma unroll
-        for (int u = kTile - 1; u >= 0; --u) {
-          const float2 ev = eb[b][u][lane];
-          const double e = r == 0 ? ev.x : ev.y;
-          acc_e += e;
+        for (int u0 = kTile - kSum; u0 >= 0; u0 -= kSum) {
+          float2 ev[kSum];
+          double y[kSum][D];
 #pragma unroll
-          for (int c = 0; c < D; ++c) acc_ey[c] = __builtin_fma(e, ys[c][yb + u], acc_ey[c]);
+          for (int u = kSum - 1; u >= 0; --u) {
+            ev[u] = eb[b][u0 + u][lane];
+#pragma unroll
+            for (int c = 0; c < D; ++c) y[u][c] = ys[c][yb + u0 + u];
+          }
+          __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+          for (int u = kSum - 1; u >= 0; --u) {
+            const double e = r == 0 ? ev[u].x : ev[u].y;
+            acc_e += e;
+#pragma unroll
+            for (int c = 0; c < D; ++c) acc_ey[c] = __builtin_fma(e, y[u][c], acc_ey[c]);
+          }
         }
       };
       for (;;) {
