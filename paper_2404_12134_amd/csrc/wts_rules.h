@@ -75,10 +75,11 @@ inline double sweep_time(const SweepLoad& l, int cus, int waves, double q, bool 
   const double t = q * l.chain + 120.0;
   if (l.items <= slots) return t;
   const double work = (q * l.steps + 120.0 * l.items) / slots;
-  const double tail = q * std::min(0.36 * l.longest, 2.0 * (l.longest - l.steps / l.items));
+  const double mean = l.steps / l.items;
+  const double tail = q * std::min(0.28 * l.longest, 1.5 * (l.longest - mean));
   const double deep = std::max(0.0, l.strips - slots / l.pairs);
-  const double wait = waves > 1 && !fp32 ? q * std::min(250.0 * deep, 0.25 * l.longest) : 0.0;
-  const double rounds = std::ceil(l.items / slots) * (q * l.shortest + 120.0);
+  const double wait = waves > 1 && !fp32 ? q * std::min(200.0 * deep, 0.2 * l.longest) : 0.0;
+  const double rounds = std::ceil(l.items / slots) * (q * (0.7 * l.shortest + 0.3 * mean) + 120.0);
   return std::max(std::max(t, work + tail + wait), rounds);
 }
 
@@ -86,10 +87,10 @@ inline double sweep_time(const SweepLoad& l, int cus, int waves, double q, bool 
 // throughput (a step of both takes q times a step of one) and slows the chain
 // of every pair's strips by as much.  q, measured: 1.4 to 1.8 in float64 with the
 // channels and rows (less for the lighter instruction mixes of Sub-DTW and of
-// value sweeps), 1.1 in float32.  Over 786 sweeps (32 shapes of 1.2 to 14 strips a
-// SIMD, of lengths that spread by half and of equal ones, d = 1, 3, 6, all kinds) the
-// choice between one and more costs 0.24 % on average against the better of
-// both, and 18 % at most.  Measured, us at 1 / 2 / 3: scores of 128 cycles of about 4k
+// value sweeps), 1.05 to 1.1 in float32.  Over 1346 sweeps (45 shapes of 1.1 to 20
+// strips a SIMD, of lengths that spread by two fifths and of equal ones, d = 1, 3, 6,
+// 8, all kinds) the choice between one and more costs 0.30 % on average against the
+// better of both, and 18 % at most.  Measured, us at 1 / 2 / 3: scores of 128 cycles of about 4k
 // (d = 3) 1524 / 1743 / 1750, in float32 1407 / 1178 / 1170, of 1000 of 1000 (d = 1)
 // 566 / 517 / 505; Sub-DTW of 256 of 4k (d = 1) 2684 / 2332 / 2197.
 // A third gains 3 to 10 % where there are strips enough and the mix is light.
@@ -98,7 +99,7 @@ inline int sweep_waves(const SweepLoad& l, int kind, int cus, int d, int rho, bo
   if (l.items <= simds) return 1;
   double q = kind == kSweepValues ? 1.23 + 0.06 * d : kind == kSweepSub ? 1.36 + 0.04 * d : 1.43 + 0.05 * d;
   q = std::min(1.03 * (rho == 5 ? q + 0.07 : q), 1.78);
-  if (fp32) q = kind == kSweepValues || kind == kSweepSub ? 1.1 : 1.15;
+  if (fp32) q = kind == kSweepValues || kind == kSweepSub ? 1.05 : 1.1;
   if (sweep_time(l, cus, 1, 1.0, fp32) <= sweep_time(l, cus, 2, q, fp32)) return 1;
   if (kind == kSweepValues && d <= 4) return 3;
   const bool light = fp32 ? kind != kSweepScores || l.items > 6 * simds : kind == kSweepSub && d <= 4;
